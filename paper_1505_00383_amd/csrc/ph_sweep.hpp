@@ -47,49 +47,47 @@ PH_SW Num term_sweep(int k, const uint32_t *fw, Num c, XF &&X, PF &&P)
         else
             return X(fac_var(fw[l]));
     };
-    Num q[KMAX];
-    Num cf = c;
+    // q[l] = forward product before factor l; run ends as the value.  (Looking
+    // up the last forward product and coordinate by the term's own count
+    // afterwards took a select per factor and limb: double double, n = 10 with
+    // terms of up to 10 factors, 34940 points: 418 us with, 311 us without.)
+    Num q[JAC ? KMAX : 1];
+    Num run = c;
 #pragma unroll
     for (int l = 0; l < KMAX; ++l) {
         if (l < k) {
             const Num xl = X(fac_var(fw[l]));
             if constexpr (KEEPX) xv[l] = xl;
             const int e = fac_exp(fw[l]);
-            for (int r = 1; r < e; ++r) cf = num_mul(cf, xl);
+            for (int r = 1; r < e; ++r) run = num_mul(run, xl);
         }
     }
-    q[0] = cf;
 #pragma unroll
-    for (int l = 1; l < KMAX; ++l)
-        if (l < k) q[l] = num_mul(q[l - 1], xat(l - 1));
-    // last forward product and last coordinate, selected with static indices
-    Num last = q[0];
-    Num xlast;
-    if constexpr (KEEPX) xlast = xv[0];
-    uint32_t wlast = fw[0];
-#pragma unroll
-    for (int l = 1; l < KMAX; ++l)
-        if (l == k - 1) {
-            last = q[l];
-            wlast = fw[l];
-            if constexpr (KEEPX) xlast = xv[l];
+    for (int l = 0; l < KMAX; ++l) {
+        if (l < k) {
+            if constexpr (JAC) q[l] = run;
+            run = num_mul(run, xat(l));
         }
-    if constexpr (!KEEPX) xlast = X(fac_var(wlast));
-    Num value = num_mul(last, xlast);
+    }
     if constexpr (JAC) {
-        Num sfx = xlast;
+        Num sfx = run;  // x_{j_{l+1}} ... x_{j_{k-1}} once past the last factor
 #pragma unroll
         for (int l = KMAX - 1; l >= 0; --l) {
             if (l < k) {
-                Num part = (l == k - 1) ? q[l] : num_mul(q[l], sfx);
-                if (l < k - 1 && l > 0) sfx = num_mul(sfx, xat(l));
+                Num part = q[l];
+                if (l == k - 1) {
+                    if (l > 0) sfx = xat(l);
+                } else {
+                    part = num_mul(part, sfx);
+                    if (l > 0) sfx = num_mul(sfx, xat(l));
+                }
                 const int e = fac_exp(fw[l]);
                 if (e != 1) part = num_scale(part, (double)e);
                 P(l, fw[l], part);
             }
         }
     }
-    return value;
+    return run;
 }
 
 }  // namespace ph
