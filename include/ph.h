@@ -233,13 +233,15 @@ int ph_eval_autotune(ph_system *target, const ph_system *start, const double gam
  *                   more than the launch's kernel fits on a CU at once
  *                   (registers, LDS), so every workgroup of a launch starts
  *                   with it
- *   lanes_per_path  lanes that share one path: 4, 8, 16 or 32; 0 selects
- *                   the natural count (the next power of two >= n, at least
- *                   4), doubled when the paths at their natural count would
- *                   fill less than one wave per SIMD.  With 2 or 4 times the
- *                   natural count, 2 or 4 lanes share each equation's term
- *                   sweeps (results unchanged bit for bit), which spreads few
- *                   paths over more waves
+ *   lanes_per_path  lanes that share one path: 4, 8, 16 or 32; 0 selects a
+ *                   whole wave while the paths are few (up to about 2 k paths
+ *                   of n <= 4, 16 k of n <= 8, 22 k beyond), else the natural
+ *                   count (the next power of two >= n, at least 4).  With 2
+ *                   or 4 times the natural count, 2 or 4 lanes share each
+ *                   equation's term sweeps; a whole wave shares the sweeps of
+ *                   all equations and the columns of the solve (results
+ *                   unchanged bit for bit), which shortens the iterations of
+ *                   few paths
  */
 #define PH_SCHED_PERSISTENT 0
 #define PH_SCHED_GRAPH 1

@@ -60,9 +60,10 @@ def kept_asm(src: str) -> str | None:
     return path
 
 
-# track_unit.hip holds the tracker launchers for one (residual limbs, FP64
-# solves) pair per compilation: six objects built in parallel.
-TRACK_UNIT = "track_unit.hip"
+# track_unit.hip and track_wide_unit.hip hold the tracker launchers for one
+# (residual limbs, FP64 solves) pair per compilation: six objects each, built in
+# parallel.
+TRACK_UNITS = {"track_unit.hip": "track", "track_wide_unit.hip": "track_wide"}
 TRACK_VARIANTS = [(L, m) for L in (1, 2, 4) for m in (1, 0)]
 
 
@@ -70,12 +71,12 @@ def sources():
     """(source, object name, extra flags) of every compilation."""
     out = []
     # the heaviest compilations first: the tracker units, then eval.hip
-    for f in sorted(os.listdir(CSRC), key=lambda f: (f != TRACK_UNIT, f != "eval.hip", f)):
+    for f in sorted(os.listdir(CSRC), key=lambda f: (f not in TRACK_UNITS, f != "eval.hip", f)):
         if not f.endswith((".hip", ".cpp")):
             continue
-        if f == TRACK_UNIT:
+        if f in TRACK_UNITS:
             for L, m in TRACK_VARIANTS:
-                out.append((f, f"track_l{L}{'m' if m else 'p'}.o",
+                out.append((f, f"{TRACK_UNITS[f]}_l{L}{'m' if m else 'p'}.o",
                             [f"-DPH_TRACK_L={L}", f"-DPH_TRACK_MIXED={m}"]))
         else:
             out.append((f, f + ".o", []))

@@ -77,6 +77,34 @@ struct MTerm {
 };
 static_assert(sizeof(MTerm) == 256, "MTerm is one 256-byte record");
 
+// Term schedule of the tracker kernel that gives a wave to one path (built by
+// build_wide, see wide_table.cpp): per round of 64 terms and lane the term's
+// shape (factors in bits 0..7, start term in bit 8; WIDE_NONE: no term), its
+// factor words and coefficient limbs; per chunk of WIDE_ROUNDS rounds {first
+// list step, list steps, a multiple of four, steps with partials}; per list
+// step and lane {a partial's slot, the matrix entry it is added to in bits 16.. and whether it is
+// the entry's first and last one of the chunk (zero: nothing to add); the slot
+// of a term's value, WIDE_NONE for nothing}.
+constexpr int WIDE_ROUNDS = 2;
+constexpr uint32_t WIDE_NONE = 0xffffffffu;
+constexpr uint32_t WIDE_FIRST = 0x80000000u, WIDE_LAST = 0x40000000u, WIDE_ENTRY = 0x7ffu;
+struct WideTable {
+    int rounds = 0;
+    std::vector<uint32_t> meta, fac;
+    std::vector<uint2> list;
+    std::vector<double> coef;
+    std::vector<int4> chunk;
+};
+
+// The device copy of a WideTable.
+struct WideDev {
+    const uint32_t *meta, *fac;
+    const uint2 *list;
+    const double *coef;
+    const int4 *chunk;
+    int32_t rounds, chunks;
+};
+
 struct DevTable {
     int n_eq = 0, n_var = 0, kmax = 0;
     int emax = 0;                // largest exponent of a target/start term
@@ -96,6 +124,8 @@ struct DevTable {
     uint32_t *fac = nullptr;     // [n_fac]
     uint32_t *fac8 = nullptr;    // [n_terms][8]: each term's factor words, zero padded (tracker)
     double *coef = nullptr;      // [n_terms][2][4] limbs
+    bool coef_single = false;    // every coefficient is an FP64 number
+    WideDev wide{};              // square systems of n <= 32, k <= 8 (rounds 0: none)
     int32_t *zc_off = nullptr;   // [n_eq + 1] columns of each row no term touches
     int32_t *zc = nullptr;
     // the paper's unfused three-kernel design (coeff, mon, sum; an ablation):
@@ -145,6 +175,8 @@ namespace ph {
 // Build and upload the merged table of (f, g); g == nullptr selects the
 // total-degree start system g_i = x_i^{d_i} - 1.
 int build_table(const HostSystem &f, const HostSystem *g, DevTable &out);
+void build_wide(int n, const std::vector<int32_t> &eq_off, const std::vector<int4> &tdesc,
+                const std::vector<uint32_t> &fac, const std::vector<double> &coef, WideTable &w);
 void free_table(DevTable &t);
 // Table for (target, start), built on first use and cached in the target
 // (allocates and synchronises when it builds).

@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "../../include/ph.h"
+#include "ph_internal.hpp"
 
 namespace ph {
 
@@ -16,6 +17,7 @@ struct SysDesc {
     const uint32_t *fac;
     const uint32_t *fac8;    // [term][8] factor words by term index
     const double *coef;
+    WideDev wide;            // schedule of the terms over a whole wave
     const int64_t *path_ids; // multi-index number of every tracked path, or NULL (0..npaths-1)
     int64_t path_off;        // first global path index of this system (outputs)
     int64_t npaths;
@@ -54,6 +56,8 @@ struct TrackArgs {
     void *state;                // round schedule: per-lane slot state
     double *hist;               // predictor orders 2..4: three older points per lane slot,
     int64_t hist_ld;            //   rows [q][re,im][limb], hist_ld = lane slots of the launch
+    int coef_single;            // every coefficient of the launch's systems is an FP64 number
+    int wide_cols;              // a wave per path: history columns of a workgroup (its rows)
     int rounds;                 // round schedule: rounds per launch
     unsigned long long budget;  // round schedule: wall-clock ticks per launch (0: rounds only)
     ph_track_opts o;
@@ -69,6 +73,12 @@ int track_launch(const TrackArgs &a, int prec, int kmax, int blocks, size_t lds,
 // instantiated in track_unit.hip.
 template <int L, bool MIXED>
 int track_launch_t(const TrackArgs &a, int kmax, int blocks, size_t lds, hipStream_t st, int *occ);
+// The same for the kernel that gives a wave to one path (track_wide_unit.hip).
+template <int L, bool MIXED>
+int track_wide_launch_t(const TrackArgs &a, int kmax, int blocks, size_t lds, hipStream_t st, int *occ);
+int track_wide_launch(const TrackArgs &a, int prec, int kmax, int blocks, size_t lds, hipStream_t st,
+                      int *occ = nullptr);
+size_t track_wide_lds_bytes(int prec, int mixed, int np_max, int kmax);
 template <int L>
 size_t slot_bytes_t();
 template <int L>

@@ -1,5 +1,5 @@
 // ph_track_dev.hpp -- device code of the path tracker (included by the
-// per-precision translation units track_l1.hip, track_l2.hip, track_l4.hip).
+// compilations of track_unit.hip and track_wide_unit.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -10,6 +10,27 @@
 #include "ph_track.hpp"
 
 namespace ph {
+
+// Reads of the term tables.  Their addresses come from memory (SysDesc), so the
+// compiler cannot tell that they are global and would read them with flat
+// loads, which count as LDS operations too: every wait for an LDS operand then
+// waits for the next term's record as well (measured: 8 k of the 16 k cycles
+// of an n = 8 evaluation on a lone wave).
+template <class T>
+__device__ __forceinline__ T tab_read(const T *p, int64_t i)
+{
+    return reinterpret_cast<const __attribute__((address_space(1))) T *>(reinterpret_cast<uintptr_t>(p))[i];
+}
+typedef int vec4i __attribute__((ext_vector_type(4)));
+typedef unsigned vec2u __attribute__((ext_vector_type(2)));
+
+// Next path index of a class queue.
+__device__ __forceinline__ unsigned long long queue_pop(unsigned long long *q)
+{
+    return __hip_atomic_fetch_add(
+        reinterpret_cast<__attribute__((address_space(1))) unsigned long long *>(reinterpret_cast<uintptr_t>(q)), 1ull,
+        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
 
 // Partner value for step O (1, 2, 4, 8, 16) of a group reduction.  The
 // first four steps stay inside a 16-lane row and use DPP moves (quad
@@ -127,6 +148,55 @@ __device__ __forceinline__ C<L> gbcast_c(C<L> v, bool mine)
     return r;
 }
 
+// Running sum of L-limb values, limb by limb: the rounding error of each
+// limb's sum joins the next limb (TwoSum), the last limb is summed plainly, and
+// the limbs are renormalised once at the end.  Nothing but the last limb
+// rounds, and what a term adds to the dependency chain is one addition per
+// limb, where a normalised addition is a chain of thirteen (double double).
+template <int L>
+__device__ __forceinline__ void acc_add(R<L> &s, const R<L> &u)
+{
+    if constexpr (L == 1) {
+        s.v[0] += u.v[0];
+    } else if constexpr (L == 2) {
+        double e;
+        two_sum(s.v[0], u.v[0], s.v[0], e);
+        s.v[1] += e + u.v[1];
+    } else {
+        double e0, e1, f, g, h, k;
+        two_sum(s.v[0], u.v[0], s.v[0], e0);
+        two_sum(s.v[1], u.v[1], s.v[1], e1);
+        two_sum(s.v[1], e0, s.v[1], f);
+        two_sum(s.v[2], u.v[2], s.v[2], g);
+        two_sum(s.v[2], e1, s.v[2], h);
+        two_sum(s.v[2], f, s.v[2], k);
+        s.v[3] += (u.v[3] + g) + (h + k);
+    }
+}
+
+template <int L>
+__device__ __forceinline__ R<L> acc_value(const R<L> &s)
+{
+    if constexpr (L == 1) {
+        return s;
+    } else if constexpr (L == 2) {
+        R<2> r;
+        two_sum(s.v[0], s.v[1], r.v[0], r.v[1]);
+        return r;
+    } else {
+        // limbs may overlap and cancel against each other: three passes
+        // leave the sum in the leading limbs
+        R<4> r = s;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            two_sum(r.v[2], r.v[3], r.v[2], r.v[3]);
+            two_sum(r.v[1], r.v[2], r.v[1], r.v[2]);
+            two_sum(r.v[0], r.v[1], r.v[0], r.v[1]);
+        }
+        return r;
+    }
+}
+
 template <int L>
 __device__ __forceinline__ double c_absd(C<L> a)
 {
@@ -211,6 +281,112 @@ __device__ R<L> half_sqrt3_t()
     return r_mul_d<L>(r_sqrt<L>(three), 0.5);
 }
 
+template <int L>
+__device__ __forceinline__ C<L> c_sel(bool m, const C<L> &a, const C<L> &b)
+{
+    C<L> z;
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+        z.re.v[l] = m ? a.re.v[l] : b.re.v[l];
+        z.im.v[l] = m ? a.im.v[l] : b.im.v[l];
+    }
+    return z;
+}
+
+// The products of term_sweep (ph_sweep.hpp) for a wave whose lanes sweep terms
+// of at most K factors each: one straight run of products in which a lane with
+// fewer factors keeps its value by a select (HOM: every lane has K factors).
+// A double-double product is a chain of fourteen dependent operations, and
+// with a branch around each product nothing overlaps: term_sweep took 5.4 k
+// cycles per term of three factors on a lone wave.  Powers and scalings run as
+// long as any lane needs them.
+template <int K, bool HOM, int L, class XF, class PF>
+__device__ __forceinline__ C<L> lane_sweep(int k, const uint32_t *fw, C<L> run, XF &&X, PF &&P)
+{
+    constexpr bool KEEPX = L <= 2 || K <= 2;  // quad double: few registers
+    C<L> xv[KEEPX ? K : 1], q[K];
+    auto xat = [&](int l) -> C<L> {
+        if constexpr (KEEPX)
+            return xv[l];
+        else
+            return X(fac_var(fw[l]));
+    };
+    if constexpr (KEEPX) {
+#pragma unroll
+        for (int l = 0; l < K; ++l) xv[l] = X(fac_var(fw[l]));
+    }
+#pragma unroll
+    for (int l = 0; l < K; ++l) {
+        const int e = l < k ? fac_exp(fw[l]) : 1;
+        for (int r = 1; __any(r < e); ++r) run = c_sel<L>(r < e, c_mul<L>(run, xat(l)), run);
+    }
+#pragma unroll
+    for (int l = 0; l < K; ++l) {
+        q[l] = run;
+        const C<L> p = c_mul<L>(run, xat(l));
+        run = HOM ? p : c_sel<L>(l < k, p, run);
+    }
+    C<L> sfx = xat(K - 1);
+#pragma unroll
+    for (int l = K - 1; l >= 0; --l) {
+        C<L> part = q[l];
+        if (l < K - 1) {
+            const C<L> p = c_mul<L>(part, sfx);
+            part = HOM ? p : c_sel<L>(l < k - 1, p, part);
+            if (l > 0) {
+                const C<L> s = c_mul<L>(sfx, xat(l));
+                sfx = HOM ? s : c_sel<L>(l < k - 1, s, xat(l));
+            }
+        }
+        const int e = fac_exp(fw[l]);
+        const bool scaled = l < k && e != 1;
+        if (__any(scaled)) part = c_sel<L>(scaled, c_mul_d<L>(part, (double)e), part);
+        if (l < k) P(l, fw[l], part);
+    }
+    return run;
+}
+
+// A term of k <= KMAX factors on every active lane: the straight sweep up to
+// four factors, term_sweep beyond.
+template <int KMAX, int L, class XF, class PF>
+__device__ __forceinline__ C<L> wave_sweep(int k, const uint32_t *fw, const C<L> &c, XF &&X, PF &&P)
+{
+    if constexpr (KMAX > 4) {
+        if (__any(k > 4)) {
+            if (k == 0) return c;
+            return term_sweep<KMAX, true, (L <= 2)>(k, fw, c, X, P);
+        }
+    }
+    // (quad double: one variant per factor count, its selects are cheap)
+    constexpr bool H = L <= 2;
+    if constexpr (KMAX > 2) {
+        if (__any(k > 3))
+            return H && __all(k == 4) ? lane_sweep<4, H, L>(k, fw, c, X, P) : lane_sweep<4, false, L>(k, fw, c, X, P);
+        if (__any(k > 2))
+            return H && __all(k == 3) ? lane_sweep<3, H, L>(k, fw, c, X, P) : lane_sweep<3, false, L>(k, fw, c, X, P);
+    }
+    if (__any(k > 1))
+        return H && __all(k == 2) ? lane_sweep<2, H, L>(k, fw, c, X, P) : lane_sweep<2, false, L>(k, fw, c, X, P);
+    if (__any(k > 0)) return lane_sweep<1, false, L>(k, fw, c, X, P);
+    return c;
+}
+
+// c t for a target term; single: the system's coefficients are FP64 numbers,
+// whose products with t are two limbs, exact (the limbs c_mul_d forms).
+template <int L>
+__device__ __forceinline__ C<L> coef_t(const C<L> &c, double t, bool single)
+{
+    if constexpr (L == 1) {
+        return c_mul_d<1>(c, t);
+    } else {
+        if (!single) return c_mul_d<L>(c, t);
+        C<L> z = c_zero<L>();
+        two_prod(c.re.v[0], t, z.re.v[0], z.re.v[1]);
+        two_prod(c.im.v[0], t, z.im.v[0], z.im.v[1]);
+        return z;
+    }
+}
+
 enum : int { PH_EMPTY = 0, PH_STEP = 1, PH_CORRECT = 2, PH_POLISH = 3, PH_RETIRED = 4 };
 
 // Everything a lane carries from one round to the next.  The path-level
@@ -257,6 +433,288 @@ __device__ __forceinline__ void lagrange_weights(int m, const double *T, double 
     }
 }
 
+// The MGS orthogonalises without normalising: with s_j = w_k^H w_j and
+// nu = w_k^H w_k, column j loses (s_j / nu) w_k, and R'(k, j) = s_j / nu is the
+// row of a unit upper triangular factor.  The products s_j do not wait for
+// the norm, no square root is taken, and the back substitution divides by
+// nothing: the chain of a column is one group sum and one reciprocal, where
+// normalised columns need the sum, a square root, a reciprocal and a second
+// sum.  The singularity test |w_k| <= eps |A|_F is made on the squares.
+
+// 1 / nu of a pivot, or false when it counts as zero: not above lim2, below
+// the normal range, or NaN.
+template <int LS>
+__device__ __forceinline__ bool mgs_pivot(const R<LS> &nu, double lim2, R<LS> &inv)
+{
+    if (!(nu.v[0] > lim2) || !(nu.v[0] >= 0x1p-1022)) return false;
+    if constexpr (LS == 1) {
+        double y = __builtin_amdgcn_rcp(nu.v[0]);
+#pragma unroll
+        for (int it = 0; it < 2; ++it) y = __builtin_fma(__builtin_fma(-nu.v[0], y, 1.0), y, y);
+        inv.v[0] = y;
+    } else {
+        inv = r_recip<LS>(nu);
+    }
+    return true;
+}
+
+// a - r q (one column entry less its projection, one unknown less a term)
+template <int LS>
+__device__ __forceinline__ C<LS> c_submul(const C<LS> &a, const C<LS> &r, const C<LS> &q)
+{
+    if constexpr (LS == 1) {
+        C<1> z;
+        z.re.v[0] = __builtin_fma(r.im.v[0], q.im.v[0], __builtin_fma(-r.re.v[0], q.re.v[0], a.re.v[0]));
+        z.im.v[0] = __builtin_fma(-r.im.v[0], q.re.v[0], __builtin_fma(-r.re.v[0], q.im.v[0], a.im.v[0]));
+        return z;
+    } else {
+        return c_sub<LS>(a, c_mul<LS>(r, q));
+    }
+}
+
+// The steps of a round that every schedule of lanes shares.  Lane i of a group
+// of NP lanes owns coordinate i of the group's path; with several groups per
+// path (ph_track_wide.hpp) each of them carries the same state and only the
+// first one writes.  hcol: the lane's column of the history buffer.
+template <int L>
+struct PathLane {
+    int i;
+    bool writes;
+    int64_t hcol;
+};
+
+// Report the path of the slot and empty the slot.
+template <int L>
+__device__ __forceinline__ void path_finish(const TrackArgs &a, Slot<L> &S, const PathLane<L> &pl, int reason)
+{
+    if (pl.writes && pl.i < S.n) {
+#pragma unroll
+        for (int l = 0; l < L; ++l) {
+            a.x_end[((int64_t)(pl.i * 2 + 0) * L + l) * a.ld_end + S.gid] = S.x.re.v[l];
+            a.x_end[((int64_t)(pl.i * 2 + 1) * L + l) * a.ld_end + S.gid] = S.x.im.v[l];
+        }
+    }
+    if (pl.writes && pl.i == 0) {
+        a.status[S.gid] = reason == PH_R_SUCCESS ? 1 : -1;
+        if (a.reason) a.reason[S.gid] = (int8_t)reason;
+        if (a.steps) a.steps[S.gid] = S.steps;
+        atomicAdd(&a.stats[0], (unsigned long long)S.steps);
+        atomicAdd(&a.stats[1], (unsigned long long)S.rejected);
+        atomicAdd(&a.stats[2], (unsigned long long)S.newton);
+        atomicAdd(&a.stats[3 + reason], 1ull);
+    }
+    S.phase = PH_EMPTY;
+    S.n = 0;
+}
+
+// Start the path with queue index id of the class (or retire the slot when
+// the queue is empty).
+template <int L>
+__device__ __forceinline__ void path_start(const TrackArgs &a, const TrackClass &cl, Slot<L> &S, const PathLane<L> &pl,
+                                           int64_t id, const R<L> &h3)
+{
+    if (id >= cl.total) {
+        S.phase = PH_RETIRED;
+        S.n = 0;
+        return;
+    }
+    int sidx = cl.sys_first;
+    while (sidx + 1 < cl.sys_end && a.sys[sidx + 1].qoff <= id) ++sidx;
+    const SysDesc &sd = a.sys[sidx];
+    S.sidx = sidx;
+    S.n = sd.n;
+    const int64_t local = id - sd.qoff;
+    S.gid = sd.path_off + local;
+    const int64_t pid = sd.path_ids ? tab_read(sd.path_ids, local) : local;
+    S.x = c_zero<L>();
+    if (pl.i < S.n) {
+        if (a.x_start) {
+#pragma unroll
+            for (int l = 0; l < L; ++l) {
+                S.x.re.v[l] = a.x_start[((int64_t)(pl.i * 2 + 0) * L + l) * a.ld_start + S.gid];
+                S.x.im.v[l] = a.x_start[((int64_t)(pl.i * 2 + 1) * L + l) * a.ld_start + S.gid];
+            }
+        } else {
+            const int d = sd.deg[pl.i];
+            const int k = (int)((pid / sd.radix[pl.i]) % d);
+            S.x = root_of_unity<L>(d, k, h3);
+        }
+    }
+    S.xp = S.x;
+    S.xh = S.x;
+    S.t = S.tp = 0.0;
+    S.h = a.o.h_init;
+    S.succ = S.it = S.have_prev = S.pit = S.nh = 0;
+    S.steps = S.rejected = S.newton = 0;
+    S.phase = PH_STEP;
+}
+
+// Older history points of this lane's coordinate: [q][re,im][limb] rows of
+// the history buffer.
+template <int L>
+__device__ __forceinline__ C<L> hist_get(const TrackArgs &a, const PathLane<L> &pl, int q)
+{
+    C<L> z;
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+        z.re.v[l] = a.hist[((int64_t)(q * 2 + 0) * L + l) * a.hist_ld + pl.hcol];
+        z.im.v[l] = a.hist[((int64_t)(q * 2 + 1) * L + l) * a.hist_ld + pl.hcol];
+    }
+    return z;
+}
+
+template <int L>
+__device__ __forceinline__ void hist_put(const TrackArgs &a, const PathLane<L> &pl, int q, const C<L> &z)
+{
+    if (!pl.writes) return;
+#pragma unroll
+    for (int l = 0; l < L; ++l) {
+        a.hist[((int64_t)(q * 2 + 0) * L + l) * a.hist_ld + pl.hcol] = z.re.v[l];
+        a.hist[((int64_t)(q * 2 + 1) * L + l) * a.hist_ld + pl.hcol] = z.im.v[l];
+    }
+}
+
+// Predict the next point (phase STEP becomes CORRECT, or the path ends).
+template <int L>
+__device__ __forceinline__ void path_predict(const TrackArgs &a, Slot<L> &S, const PathLane<L> &pl)
+{
+    if (S.steps >= a.o.max_steps) {
+        path_finish<L>(a, S, pl, PH_R_MAX_STEPS);
+        return;
+    }
+    ++S.steps;
+    if (S.h > 1.0 - S.t) S.h = 1.0 - S.t;
+    S.t1 = S.t + S.h;
+    if (S.t1 >= 1.0 - 1e-15) S.t1 = 1.0;
+    const int mo = S.nh < a.o.predictor_order ? S.nh : a.o.predictor_order;
+    if (mo >= 2) {
+        // the current point and mo previous accepted points
+        const double T[5] = {S.t, S.tp, S.tq[0], S.tq[1], S.tq[2]};
+        double w[5];
+        lagrange_weights(mo, T, S.t1, w);
+        C<L> acc = c_add<L>(c_mul_d<L>(S.x, w[0]), c_mul_d<L>(S.xp, w[1]));
+        for (int j = 2; j <= mo; ++j) acc = c_add<L>(acc, c_mul_d<L>(hist_get<L>(a, pl, j - 2), w[j]));
+        S.xh = acc;
+    } else if (S.have_prev) {
+        const double r = (S.t1 - S.t) / (S.t - S.tp);
+        S.xh = c_add<L>(S.x, c_mul_d<L>(c_sub<L>(S.x, S.xp), r));
+    } else {
+        S.xh = S.x;
+    }
+    S.it = 0;
+    S.dprev = 0.0;
+    S.phase = PH_CORRECT;
+}
+
+// Decide about the path after a Newton step: dxi is the lane's component of
+// the update, sing a rank-deficient Jacobian, res the lane's residual and fro2
+// the squared Jacobian norm where the Newton system was formed.
+template <int L, int NP, int LS>
+__device__ __forceinline__ void path_decide(const TrackArgs &a, Slot<L> &S, const PathLane<L> &pl, const C<LS> &dxi,
+                                            bool sing, const C<LS> &res, double fro2)
+{
+    const ph_track_opts &o = a.o;
+    const int i = pl.i;
+    if (S.phase == PH_CORRECT) {
+        ++S.newton;
+        bool accept = false, reject = false;
+        double xn = INFINITY;  // norm of the corrected point
+        if (sing) {
+            reject = true;
+        } else {
+            S.xh = widen_add<L, LS>(S.xh, dxi);
+            const double dn = gmax_d<NP>(i < S.n ? c_absd<LS>(dxi) : 0.0);
+            xn = gmax_d<NP>(i < S.n ? c_absd<L>(S.xh) : 0.0);
+            const double hres = gmax_d<NP>(i < S.n ? c_absd<LS>(res) : 0.0);
+            const double fro = sqrt(fro2);
+            const double sx = xn > 1.0 ? xn : 1.0;
+            if (dn != dn || xn != xn) {
+                reject = true;
+            } else if (dn <= o.tol_dx * sx && hres <= o.tol_res * fro * sx) {
+                accept = true;
+            } else if (S.it >= 1 && dn > S.dprev) {
+                reject = true;
+            } else {
+                S.dprev = dn;
+                ++S.it;
+                if (S.it >= o.max_newton) reject = true;
+            }
+        }
+        if (accept) {
+            if (o.predictor_order >= 2) {
+                // shift the history: older points move down, x_p joins
+                if (S.nh >= 3) hist_put<L>(a, pl, 2, hist_get<L>(a, pl, 1));
+                if (S.nh >= 2) hist_put<L>(a, pl, 1, hist_get<L>(a, pl, 0));
+                hist_put<L>(a, pl, 0, S.xp);
+                S.tq[2] = S.tq[1];
+                S.tq[1] = S.tq[0];
+                S.tq[0] = S.tp;
+            }
+            S.tp = S.t;
+            S.xp = S.x;
+            S.have_prev = 1;
+            if (S.nh < 4) ++S.nh;
+            S.t = S.t1;
+            S.x = S.xh;
+            if (++S.succ >= o.expand_after) {
+                S.h = S.h * o.expand;
+                if (S.h > o.h_max) S.h = o.h_max;
+                S.succ = 0;
+            }
+            S.phase = (S.t == 1.0) ? PH_POLISH : PH_STEP;
+            S.pit = 0;
+            S.dprev = INFINITY;
+        } else if (reject) {
+            ++S.rejected;
+            S.h *= o.shrink;
+            S.succ = 0;
+            S.phase = PH_STEP;
+            if (S.h < o.h_min) path_finish<L>(a, S, pl, sing ? PH_R_SINGULAR : PH_R_STEP_UNDERFLOW);
+        }
+        if (accept || reject) {
+            if (S.phase != PH_EMPTY) {
+                // an accepted point is the one whose norm is known; where
+                // that is finite the point has no bad component
+                bool bad = false;
+                if (reject || !isfinite(xn)) {
+                    bad = gmax_d<NP>((i < S.n && c_bad<L>(S.x)) ? 1.0 : 0.0) > 0.0;
+                    xn = gmax_d<NP>(i < S.n ? c_absd<L>(S.x) : 0.0);
+                }
+                if (bad) path_finish<L>(a, S, pl, PH_R_NAN);
+                else if (xn > o.diverge_norm) path_finish<L>(a, S, pl, PH_R_DIVERGED);
+            }
+        }
+    } else if (S.phase == PH_POLISH) {
+        // Newton on f at t = 1 until the update meets polish_tol, stops
+        // halving, or polish_max steps were taken; an update that is not
+        // finite ends the polish without being applied
+        bool done = false;
+        if (sing) {
+            done = true;
+        } else {
+            const double dn = gmax_d<NP>(i < S.n ? c_absd<LS>(dxi) : 0.0);
+            if (!isfinite(dn) || (S.pit > 0 && !(dn < 0.5 * S.dprev))) {
+                done = true;
+            } else {
+                S.x = widen_add<L, LS>(S.x, dxi);
+                ++S.newton;
+                const double xn = gmax_d<NP>(i < S.n ? c_absd<L>(S.x) : 0.0);
+                if (dn <= a.polish_tol * (xn > 1.0 ? xn : 1.0)) done = true;
+                S.dprev = dn;
+                ++S.pit;
+                if (S.pit >= o.polish_max) done = true;
+            }
+        }
+        S.xh = S.x;
+        if (done) {
+            // the endpoint must be finite and within diverge_norm
+            const bool bad = gmax_d<NP>((i < S.n && c_bad<L>(S.x)) ? 1.0 : 0.0) > 0.0;
+            const double xe = gmax_d<NP>(i < S.n ? c_absd<L>(S.x) : 0.0);
+            path_finish<L>(a, S, pl, bad ? PH_R_NAN : (xe > o.diverge_norm ? PH_R_DIVERGED : PH_R_SUCCESS));
+        }
+    }
+}
+
 // Run at most max_rounds rounds of the tracker on the slots of this wave, or
 // until every slot is retired (the queue of the class is empty).  Returns
 // true when the wave is retired.
@@ -269,7 +727,6 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
     const int g = lane / NP;
     const int i = lane % NP;
     const int base = g * NP;
-    const ph_track_opts &o = a.o;
     const R<L> h3 = half_sqrt3_t<L>();
     // LDS views: xg = the group's current iterate, W(j, row) = entry of the
     // augmented matrix [J | -H] (column j = NP holds -H)
@@ -278,54 +735,7 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
         return wsh + (((size_t)g * (NP + 1) + j) * NP + row) * 2 * LS;
     };
 
-    int phase = S.phase, sidx = S.sidx, n = S.n, succ = S.succ, it = S.it;
-    int have_prev = S.have_prev, pit = S.pit, nh = S.nh;
-    double tq0 = S.tq[0], tq1 = S.tq[1], tq2 = S.tq[2];
-    const int order = o.predictor_order;
-    // older history points of this lane's coordinate: [q][re,im][limb] rows
-    // of the history buffer, one column per lane slot
-    const int64_t hcol = (int64_t)blockIdx.x * 64 + lane;
-    auto hist_get = [&](int q) -> C<L> {
-        C<L> z;
-#pragma unroll
-        for (int l = 0; l < L; ++l) {
-            z.re.v[l] = a.hist[((int64_t)(q * 2 + 0) * L + l) * a.hist_ld + hcol];
-            z.im.v[l] = a.hist[((int64_t)(q * 2 + 1) * L + l) * a.hist_ld + hcol];
-        }
-        return z;
-    };
-    auto hist_put = [&](int q, const C<L> &z) {
-#pragma unroll
-        for (int l = 0; l < L; ++l) {
-            a.hist[((int64_t)(q * 2 + 0) * L + l) * a.hist_ld + hcol] = z.re.v[l];
-            a.hist[((int64_t)(q * 2 + 1) * L + l) * a.hist_ld + hcol] = z.im.v[l];
-        }
-    };
-    int32_t steps = S.steps, rejected = S.rejected, newton = S.newton;
-    int64_t gid = S.gid;
-    double t = S.t, tp = S.tp, t1 = S.t1, h = S.h, dprev = S.dprev;
-    C<L> x = S.x, xp = S.xp, xh = S.xh;
-
-    auto finish = [&](int reason) {
-        if (i < n) {
-#pragma unroll
-            for (int l = 0; l < L; ++l) {
-                a.x_end[((int64_t)(i * 2 + 0) * L + l) * a.ld_end + gid] = x.re.v[l];
-                a.x_end[((int64_t)(i * 2 + 1) * L + l) * a.ld_end + gid] = x.im.v[l];
-            }
-        }
-        if (i == 0) {
-            a.status[gid] = reason == PH_R_SUCCESS ? 1 : -1;
-            if (a.reason) a.reason[gid] = (int8_t)reason;
-            if (a.steps) a.steps[gid] = steps;
-            atomicAdd(&a.stats[0], (unsigned long long)steps);
-            atomicAdd(&a.stats[1], (unsigned long long)rejected);
-            atomicAdd(&a.stats[2], (unsigned long long)newton);
-            atomicAdd(&a.stats[3 + reason], 1ull);
-        }
-        phase = PH_EMPTY;
-        n = 0;
-    };
+    const PathLane<L> pl{i, true, (int64_t)blockIdx.x * 64 + lane};
 
     bool retired = false;
     const long long t_start = a.budget ? wall_clock64() : 0;  // time-budgeted launches
@@ -333,97 +743,39 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
     // read again only when the slot moves to another system: the term-table
     // pointers, gamma, and this lane's equation and term range
     int k_sidx = -1, k_n = -1;
-    const int4 *k_tdesc = nullptr;
+    const vec4i *k_tdesc = nullptr;
     const double *k_coef = nullptr;
     const uint32_t *k_fac8 = nullptr;
     double k_gre = 0.0, k_gim = 0.0;
     int k_sub = NP, k_s0 = 0, k_s1 = 0;
     for (int round = 0; round < max_rounds; ++round) {
         // ---- refill: pop a path from the device queue of this class -------
-        if (phase == PH_EMPTY) {
+        if (S.phase == PH_EMPTY) {
             unsigned long long id = 0;
-            if (i == 0) id = atomicAdd(cl.queue, 1ull);
+            if (i == 0) id = queue_pop(cl.queue);
             id = __shfl(id, base);
-            if ((int64_t)id >= cl.total) {
-                phase = PH_RETIRED;
-                n = 0;
-            } else {
-                const int64_t q = (int64_t)id;
-                sidx = cl.sys_first;
-                while (sidx + 1 < cl.sys_end && a.sys[sidx + 1].qoff <= q) ++sidx;
-                const SysDesc &sd = a.sys[sidx];
-                n = sd.n;
-                const int64_t local = q - sd.qoff;
-                gid = sd.path_off + local;
-                const int64_t pid = sd.path_ids ? sd.path_ids[local] : local;
-                x = c_zero<L>();
-                if (i < n) {
-                    if (a.x_start) {
-#pragma unroll
-                        for (int l = 0; l < L; ++l) {
-                            x.re.v[l] = a.x_start[((int64_t)(i * 2 + 0) * L + l) * a.ld_start + gid];
-                            x.im.v[l] = a.x_start[((int64_t)(i * 2 + 1) * L + l) * a.ld_start + gid];
-                        }
-                    } else {
-                        const int d = sd.deg[i];
-                        const int k = (int)((pid / sd.radix[i]) % d);
-                        x = root_of_unity<L>(d, k, h3);
-                    }
-                }
-                xp = x;
-                xh = x;
-                t = tp = 0.0;
-                h = o.h_init;
-                succ = it = have_prev = pit = nh = 0;
-                steps = rejected = newton = 0;
-                phase = PH_STEP;
-            }
+            path_start<L>(a, cl, S, pl, (int64_t)id, h3);
         }
-        const bool any_bad = gmax_d<NP>(c_bad<L>(x) ? 1.0 : 0.0) > 0.0;
-        if (phase == PH_STEP && steps == 0) {
-            if (o.h_min > o.h_init) finish(PH_R_STEP_UNDERFLOW);
-            else if (any_bad) finish(PH_R_NAN);
+        const bool any_bad = gmax_d<NP>(c_bad<L>(S.x) ? 1.0 : 0.0) > 0.0;
+        if (S.phase == PH_STEP && S.steps == 0) {
+            if (a.o.h_min > a.o.h_init) path_finish<L>(a, S, pl, PH_R_STEP_UNDERFLOW);
+            else if (any_bad) path_finish<L>(a, S, pl, PH_R_NAN);
         }
         // ---- stop when every slot of the wave is retired ------------------
-        if (__all(phase == PH_RETIRED)) {
+        if (__all(S.phase == PH_RETIRED)) {
             retired = true;
             break;
         }
 
         // ---- predictor ----------------------------------------------------
-        if (phase == PH_STEP) {
-            if (steps >= o.max_steps) {
-                finish(PH_R_MAX_STEPS);
-            } else {
-                ++steps;
-                if (h > 1.0 - t) h = 1.0 - t;
-                t1 = t + h;
-                if (t1 >= 1.0 - 1e-15) t1 = 1.0;
-                const int mo = nh < order ? nh : order;
-                if (mo >= 2) {
-                    // the current point and mo previous accepted points
-                    const double T[5] = {t, tp, tq0, tq1, tq2};
-                    double w[5];
-                    lagrange_weights(mo, T, t1, w);
-                    C<L> acc = c_add<L>(c_mul_d<L>(x, w[0]), c_mul_d<L>(xp, w[1]));
-                    for (int j = 2; j <= mo; ++j) acc = c_add<L>(acc, c_mul_d<L>(hist_get(j - 2), w[j]));
-                    xh = acc;
-                } else if (have_prev) {
-                    const double r = (t1 - t) / (t - tp);
-                    xh = c_add<L>(x, c_mul_d<L>(c_sub<L>(x, xp), r));
-                } else {
-                    xh = x;
-                }
-                it = 0;
-                dprev = 0.0;
-                phase = PH_CORRECT;
-            }
-        }
-        const bool busy = phase == PH_CORRECT || phase == PH_POLISH;
-        const double tt = phase == PH_POLISH ? 1.0 : t1;
+        if (S.phase == PH_STEP) path_predict<L>(a, S, pl);
+        const int n = S.n, sidx = S.sidx;
+        const C<L> xh = S.xh;
+        const bool busy = S.phase == PH_CORRECT || S.phase == PH_POLISH;
+        const double tt = S.phase == PH_POLISH ? 1.0 : S.t1;
         if (busy && (sidx != k_sidx || n != k_n)) {
             const SysDesc &sd = a.sys[sidx];
-            k_tdesc = sd.tdesc;
+            k_tdesc = reinterpret_cast<const vec4i *>(sd.tdesc);
             k_coef = sd.coef;
             k_fac8 = sd.fac8;
             k_gre = sd.gre;
@@ -434,8 +786,8 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
             if (sb4 > NP || 2 * L + sd.kmax * 2 * LS > (NP + 1) * 2 * LS) sb4 = NP;
             k_sub = sb4;
             const int e = i % sb4;
-            k_s0 = e < n ? sd.eq_off[e] : 0;
-            k_s1 = e < n ? sd.eq_off[e + 1] : 0;
+            k_s0 = e < n ? tab_read(sd.eq_off, e) : 0;
+            k_s1 = e < n ? tab_read(sd.eq_off, e + 1) : 0;
             k_sidx = sidx;
             k_n = n;
         }
@@ -500,17 +852,17 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
             // while it sweeps the current one (quad double has no registers
             // to spare for that)
             constexpr bool AHEAD = L <= 2;
-            auto fetch = [&](int s, int4 &d, C<L> &c, uint32_t (&fw)[KMAX]) {
-                d = k_tdesc[s];
+            auto fetch = [&](int s, vec4i &d, C<L> &c, uint32_t (&fw)[KMAX]) {
+                d = tab_read(k_tdesc, s);
 #pragma unroll
                 for (int l = 0; l < L; ++l) {
-                    c.re.v[l] = k_coef[(int64_t)s * 8 + l];
-                    c.im.v[l] = k_coef[(int64_t)s * 8 + 4 + l];
+                    c.re.v[l] = tab_read(k_coef, (int64_t)s * 8 + l);
+                    c.im.v[l] = tab_read(k_coef, (int64_t)s * 8 + 4 + l);
                 }
 #pragma unroll
-                for (int l = 0; l < KMAX; ++l) fw[l] = k_fac8[(int64_t)s * 8 + l];
+                for (int l = 0; l < KMAX; ++l) fw[l] = tab_read(k_fac8, (int64_t)s * 8 + l);
             };
-            int4 dn = {0, 0, 0, 0};
+            vec4i dn = {0, 0, 0, 0};
             C<L> cn = c_zero<L>();
             uint32_t fn[KMAX];
 #pragma unroll
@@ -518,7 +870,7 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
             if (AHEAD && s0 + sr < s1) fetch(s0 + sr, dn, cn, fn);
             for (int sb = s0; sb < s1; sb += nsh) {
                 const int s = sb + sr;
-                int4 d = dn;
+                vec4i d = dn;
                 C<L> c = cn;
                 uint32_t fw[KMAX];
 #pragma unroll
@@ -529,25 +881,24 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                     fetch(s, d, c, fw);
                 }
                 if (s < s1) {
-                    c = d.z ? c_mul<L>(c, gs) : c_mul_d<L>(c, tt);
-                    C<L> tv = c;
-                    if (d.x > 0) {
-                        tv = term_sweep<KMAX, true, (L <= 2)>(
+                    const C<L> ct = coef_t<L>(c, tt, a.coef_single != 0);
+                    c = __any(d.z) ? c_sel<L>(d.z != 0, c_mul<L>(c, gs), ct) : ct;
+                    const C<L> tv = wave_sweep<KMAX, L>(
                             d.x, fw, c, X, [&](int l, uint32_t w, const C<L> &part) {
-                                const C<LS> pn = narrow<LS, L>(part);
-                                if (sr == 0) {
-                                    add_part(w, pn);
-                                } else {
+                            const C<LS> pn = narrow<LS, L>(part);
+                            if (sr == 0) {
+                                add_part(w, pn);
+                            } else {
 #pragma unroll
-                                    for (int q = 0; q < LS; ++q) {
-                                        *slot(i, 2 * L + l * 2 * LS + q) = pn.re.v[q];
-                                        *slot(i, 2 * L + l * 2 * LS + LS + q) = pn.im.v[q];
-                                    }
+                                for (int q = 0; q < LS; ++q) {
+                                    *slot(i, 2 * L + l * 2 * LS + q) = pn.re.v[q];
+                                    *slot(i, 2 * L + l * 2 * LS + LS + q) = pn.im.v[q];
                                 }
-                            });
-                    }
+                            }
+                        });
                     if (sr == 0) {
-                        v = c_add<L>(v, tv);
+                        acc_add<L>(v.re, tv.re);
+                        acc_add<L>(v.im, tv.im);
                     } else {
 #pragma unroll
                         for (int q = 0; q < L; ++q) {
@@ -565,7 +916,7 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                         // order the sweep issues them (last factor first)
                         for (int q = 1; q < nsh && sb + q < s1; ++q) {
                             const int hrow = i + q * sub;
-                            const int4 d = k_tdesc[sb + q];
+                            const vec4i d = tab_read(k_tdesc, sb + q);
                             for (int l = d.x - 1; l >= 0; --l) {
                                 C<LS> pn;
 #pragma unroll
@@ -573,7 +924,7 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                                     pn.re.v[z] = *slot(hrow, 2 * L + l * 2 * LS + z);
                                     pn.im.v[z] = *slot(hrow, 2 * L + l * 2 * LS + LS + z);
                                 }
-                                add_part(k_fac8[(int64_t)(sb + q) * 8 + l], pn);
+                                add_part(tab_read(k_fac8, (int64_t)(sb + q) * 8 + l), pn);
                             }
                             C<L> tv;
 #pragma unroll
@@ -581,7 +932,8 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                                 tv.re.v[z] = *slot(hrow, z);
                                 tv.im.v[z] = *slot(hrow, L + z);
                             }
-                            v = c_add<L>(v, tv);
+                            acc_add<L>(v.re, tv.re);
+                            acc_add<L>(v.im, tv.im);
                         }
                     }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -589,7 +941,8 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                 }
             }
-            if (sr == 0) lds_put<LS>(W(NP, i), narrow<LS, L>(c_sub<L>(c_zero<L>(), v)));
+            if (sr == 0)
+                lds_put<LS>(W(NP, i), narrow<LS, L>(C<L>{r_neg<L>(acc_value<L>(v.re)), r_neg<L>(acc_value<L>(v.im))}));
         }
         if (nsh > 1 && sr > 0) {
 #pragma unroll
@@ -602,240 +955,93 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
         // ---- correct: MGS least squares on [J | -H], row i in lane i ------
         // residual at the point where the Newton system is formed (the
         // convergence test compares it with ||J||_F, Section 2)
-        const double hres = gmax_d<NP>((busy && i < n) ? c_absd<LS>(lds_get<LS>(W(NP, i))) : 0.0);
+        const C<LS> res = lds_get<LS>(W(NP, i));
         double fro = 0.0;
 #pragma unroll
         for (int j = 0; j < NP; ++j) {
             C<LS> w = lds_get<LS>(W(j, i));
             fro += w.re.v[0] * w.re.v[0] + w.im.v[0] * w.im.v[0];
         }
-        fro = sqrt(gsum_d<NP>(fro));
+        fro = gsum_d<NP>(fro);
+        const double lim2 = a.eps_sing * a.eps_sing * fro;
         bool sing = false;
         C<LS> acc = c_zero<LS>();  // r_{i,rhs}, then the back-substitution value
         // the column loops address LDS only, so they stay rolled (code size)
 #pragma unroll 1
-        for (int k = 0; k < n; ++k) {
-            {  // group-uniform
-                C<LS> wk = lds_get<LS>(W(k, i));
-                R<LS> nr = gsum_r<NP, LS>(c_abs2<LS>(wk));
-                R<LS> rkk, inv;
-                if constexpr (LS == 1) {
-                    // FP64: the norm and its reciprocal from one reciprocal
-                    // square root refined by two coupled Newton steps
-                    // (Goldschmidt: g -> sqrt(x), h -> 1 / (2 sqrt(x))), in
-                    // place of a square root and a division in series
-                    const double x = nr.v[0];
-                    const double y = __builtin_amdgcn_rsq(x);
-                    double g = x * y, h = 0.5 * y;
-#pragma unroll
-                    for (int it = 0; it < 2; ++it) {
-                        const double r = __builtin_fma(-g, h, 0.5);
-                        g = __builtin_fma(g, r, g);
-                        h = __builtin_fma(h, r, h);
-                    }
-                    // a norm below the normal range, zero or NaN counts as zero
-                    // (singular), infinity stays NaN (singular as well)
-                    rkk.v[0] = x >= 0x1p-1022 ? g : 0.0;
-                    inv.v[0] = 2.0 * h;
-                } else {
-                    rkk = r_sqrt<LS>(nr);
+        for (int k = 0; k < n; ++k) {  // group-uniform
+            const C<LS> wk = lds_get<LS>(W(k, i));
+            R<LS> inv;
+            if (!mgs_pivot<LS>(gsum_r<NP, LS>(c_abs2<LS>(wk)), lim2, inv)) {
+                sing = true;
+                break;
+            }
+            // projection of column j: r = (w_k^H w_j) / nu (group sum),
+            // w_j -= r w_k; column k is dead after step k, so R'(k, j)
+            // goes to row j of it
+            auto proj = [&](int j) -> C<LS> {
+                double *ej = W(j, i);
+                const C<LS> wj = lds_get<LS>(ej);
+                const C<LS> r = c_mul_r<LS>(gsum_c<NP, LS>(c_cmul<LS>(wk, wj)), inv);
+                lds_put<LS>(ej, c_submul<LS>(wj, r, wk));
+                return r;
+            };
+            if constexpr (LS == 1) {
+                // FP64 solves are latency bound: four columns at a time, so
+                // their group sums interleave; the stores of R'(k, j)
+                // follow, one per lane
+                int j = k + 1;
+#pragma unroll 1
+                for (; j + 3 < n; j += 4) {
+                    const C<LS> r0 = proj(j), r1 = proj(j + 1), r2 = proj(j + 2), r3 = proj(j + 3);
+                    const int d = i - j;
+                    if (d >= 0 && d < 4)
+                        lds_put<LS>(W(k, i), d == 0 ? r0 : (d == 1 ? r1 : (d == 2 ? r2 : r3)));
                 }
-                if (!(rkk.v[0] > a.eps_sing * fro)) sing = true;
-                if (sing) break;
-                {
-                    if constexpr (LS != 1) inv = r_div<LS>(r_from<LS>(1.0), rkk);
-                    C<LS> q = c_mul_r<LS>(wk, inv);
-                    // projection of column j on q: r = q^H w_j (group sum),
-                    // w_j -= r q; column k is dead after step k, so R(k, j)
-                    // goes to row j of it
-                    auto proj = [&](int j) -> C<LS> {
-                        double *ej = W(j, i);
-                        C<LS> wj = lds_get<LS>(ej);
-                        C<LS> r = gsum_c<NP, LS>(c_cmul<LS>(q, wj));
-                        lds_put<LS>(ej, c_sub<LS>(wj, c_mul<LS>(r, q)));
-                        return r;
-                    };
-                    if constexpr (LS == 1) {
-                        // FP64 solves are latency bound: four columns at a
-                        // time, so their group sums interleave; the stores
-                        // of R(k, j) follow, one per lane
-                        int j = k + 1;
 #pragma unroll 1
-                        for (; j + 3 < n; j += 4) {
-                            const C<LS> r0 = proj(j), r1 = proj(j + 1), r2 = proj(j + 2), r3 = proj(j + 3);
-                            const int d = i - j;
-                            if (d >= 0 && d < 4)
-                                lds_put<LS>(W(k, i), d == 0 ? r0 : (d == 1 ? r1 : (d == 2 ? r2 : r3)));
-                        }
+                for (; j < n; ++j) {
+                    const C<LS> r = proj(j);
+                    if (i == j) lds_put<LS>(W(k, j), r);
+                }
+                const C<LS> r = proj(NP);
+                if (i == k) acc = r;
+            } else {
 #pragma unroll 1
-                        for (; j < n; ++j) {
-                            const C<LS> r = proj(j);
-                            if (i == j) lds_put<LS>(W(k, j), r);
-                        }
-                        const C<LS> r = proj(NP);
-                        if (i == k) acc = r;
-                    } else {
-#pragma unroll 1
-                        for (int j = k + 1; j <= NP; ++j) {
-                            if (j == n && j < NP) j = NP;  // skip the padding columns
-                            const C<LS> r = proj(j);
-                            if (i == k && j == NP) acc = r;
-                            if (j < NP && i == j) lds_put<LS>(W(k, j), r);
-                        }
-                    }
-                    if (i == k) lds_put<LS>(W(k, k), C<LS>{rkk, r_zero<LS>()});
+                for (int j = k + 1; j <= NP; ++j) {
+                    if (j == n && j < NP) j = NP;  // skip the padding columns
+                    const C<LS> r = proj(j);
+                    if (i == k && j == NP) acc = r;
+                    if (j < NP && i == j) lds_put<LS>(W(k, j), r);
                 }
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-        // back substitution R dx = r_rhs, column oriented: lane i keeps acc_i;
-        // every lane forms 1 / R(i, i) first, side by side, so that no
-        // division sits on the serial chain of the substitution
+        // back substitution R' dx = r_rhs (unit diagonal), column oriented:
+        // lane i keeps acc_i
         C<LS> dxi = c_zero<LS>();
-        R<LS> inv_i = r_zero<LS>();
-        if (!sing && i < n) inv_i = r_div<LS>(r_from<LS>(1.0), lds_get<LS>(W(i, i)).re);
 #pragma unroll 1
         for (int k = n - 1; k >= 0; --k) {
             if (!sing) {
-                C<LS> dk = c_zero<LS>();
-                if (i == k) {
-                    dk = c_mul_r<LS>(acc, inv_i);
-                    dxi = dk;
-                }
+                C<LS> dk = acc;
+                if (i == k) dxi = dk;
                 if constexpr (NP <= 16)
                     dk = gbcast_c<NP, LS>(dk, i == k);
                 else
                     dk = shfl_c<LS>(dk, base + k);
-                if (i < k) {
-                    C<LS> rik = lds_get<LS>(W(i, k));  // R(i, k), stored in column i, row k
-                    acc = c_sub<LS>(acc, c_mul<LS>(rik, dk));
-                }
+                if (i < k) acc = c_submul<LS>(acc, lds_get<LS>(W(i, k)), dk);  // R'(i, k): column i, row k
             }
         }
         if (i >= n || !busy) dxi = c_zero<LS>();
 
         // ---- per-path decisions ------------------------------------------
-        if (phase == PH_CORRECT) {
-            ++newton;
-            bool accept = false, reject = false;
-            if (sing) {
-                reject = true;
-            } else {
-                xh = widen_add<L, LS>(xh, dxi);
-                const double dn = gmax_d<NP>(i < n ? c_absd<LS>(dxi) : 0.0);
-                const double xn = gmax_d<NP>(i < n ? c_absd<L>(xh) : 0.0);
-                const double sx = xn > 1.0 ? xn : 1.0;
-                if (dn != dn || xn != xn) {
-                    reject = true;
-                } else if (dn <= o.tol_dx * sx && hres <= o.tol_res * fro * sx) {
-                    accept = true;
-                } else if (it >= 1 && dn > dprev) {
-                    reject = true;
-                } else {
-                    dprev = dn;
-                    ++it;
-                    if (it >= o.max_newton) reject = true;
-                }
-            }
-            if (accept) {
-                if (order >= 2) {
-                    // shift the history: older points move down, x_p joins
-                    if (nh >= 3) hist_put(2, hist_get(1));
-                    if (nh >= 2) hist_put(1, hist_get(0));
-                    hist_put(0, xp);
-                    tq2 = tq1;
-                    tq1 = tq0;
-                    tq0 = tp;
-                }
-                tp = t;
-                xp = x;
-                have_prev = 1;
-                if (nh < 4) ++nh;
-                t = t1;
-                x = xh;
-                if (++succ >= o.expand_after) {
-                    h = h * o.expand;
-                    if (h > o.h_max) h = o.h_max;
-                    succ = 0;
-                }
-                phase = (t == 1.0) ? PH_POLISH : PH_STEP;
-                pit = 0;
-                dprev = INFINITY;
-            } else if (reject) {
-                ++rejected;
-                h *= o.shrink;
-                succ = 0;
-                phase = PH_STEP;
-                if (h < o.h_min) finish(sing ? PH_R_SINGULAR : PH_R_STEP_UNDERFLOW);
-            }
-            if (accept || reject) {
-                if (phase != PH_EMPTY) {
-                    const bool bad = gmax_d<NP>((i < n && c_bad<L>(x)) ? 1.0 : 0.0) > 0.0;
-                    const double xn = gmax_d<NP>(i < n ? c_absd<L>(x) : 0.0);
-                    if (bad) finish(PH_R_NAN);
-                    else if (xn > o.diverge_norm) finish(PH_R_DIVERGED);
-                }
-            }
-        } else if (phase == PH_POLISH) {
-            // Newton on f at t = 1 until the update meets polish_tol, stops
-            // halving, or polish_max steps were taken; an update that is not
-            // finite ends the polish without being applied
-            bool done = false;
-            if (sing) {
-                done = true;
-            } else {
-                const double dn = gmax_d<NP>(i < n ? c_absd<LS>(dxi) : 0.0);
-                if (!isfinite(dn) || (pit > 0 && !(dn < 0.5 * dprev))) {
-                    done = true;
-                } else {
-                    x = widen_add<L, LS>(x, dxi);
-                    ++newton;
-                    const double xn = gmax_d<NP>(i < n ? c_absd<L>(x) : 0.0);
-                    if (dn <= a.polish_tol * (xn > 1.0 ? xn : 1.0)) done = true;
-                    dprev = dn;
-                    ++pit;
-                    if (pit >= o.polish_max) done = true;
-                }
-            }
-            xh = x;
-            if (done) {
-                // the endpoint must be finite and within diverge_norm
-                const bool bad = gmax_d<NP>((i < n && c_bad<L>(x)) ? 1.0 : 0.0) > 0.0;
-                const double xe = gmax_d<NP>(i < n ? c_absd<L>(x) : 0.0);
-                finish(bad ? PH_R_NAN : (xe > o.diverge_norm ? PH_R_DIVERGED : PH_R_SUCCESS));
-            }
-        }
+        path_decide<L, NP, LS>(a, S, pl, dxi, sing, res, fro);
         // round schedule with a time budget: every wave of the launch stops
         // after the round in which the budget ran out (wave-uniform clock),
         // so waves with cheap rounds do not wait for the others at the end
         // of a launch of a fixed round count
         if (a.budget && (unsigned long long)(wall_clock64() - t_start) >= a.budget) break;
     }
-    S.phase = phase;
-    S.sidx = sidx;
-    S.n = n;
-    S.succ = succ;
-    S.it = it;
-    S.have_prev = have_prev;
-    S.pit = pit;
-    S.nh = nh;
-    S.tq[0] = tq0;
-    S.tq[1] = tq1;
-    S.tq[2] = tq2;
-    S.steps = steps;
-    S.rejected = rejected;
-    S.newton = newton;
-    S.gid = gid;
-    S.t = t;
-    S.tp = tp;
-    S.t1 = t1;
-    S.h = h;
-    S.dprev = dprev;
-    S.x = x;
-    S.xp = xp;
-    S.xh = xh;
     return retired;
 }
 

@@ -46,73 +46,66 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
     std::vector<double> coef;
     int kmax = 0;
     std::vector<char> touched(nv);
-    // terms of each equation in order of their number of factors (stable):
-    // the tracker evaluates one equation per lane, and equal term shapes at
-    // equal positions keep the lanes of a wave on the same path through the
-    // sweep; the evaluation kernels are indifferent to the order
-    std::vector<int> order;
-    auto emit = [&](const HostSystem &s, int i, int sel) {
-        order.clear();
-        for (int t = s.eq_term_off[i]; t < s.eq_term_off[i + 1]; ++t) order.push_back(t);
-        std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
-            return s.term_fac_off[x + 1] - s.term_fac_off[x] < s.term_fac_off[y + 1] - s.term_fac_off[y];
-        });
-        for (int t : order) {
-            int a = s.term_fac_off[t], b = s.term_fac_off[t + 1];
-            int4 d;
-            d.x = b - a;
-            d.y = int(fac.size());
-            d.z = sel;
-            d.w = 0;
-            tdesc.push_back(d);
-            kmax = std::max(kmax, b - a);
-            for (int q = a; q < b; ++q) {
-                uint32_t w = uint32_t(s.fac_var[q]) | (uint32_t(s.fac_exp[q]) << 16);
-                if (!touched[s.fac_var[q]]) {
-                    w |= FAC_FIRST;
-                    touched[s.fac_var[q]] = 1;
-                }
-                fac.push_back(w);
-            }
-            for (int c = 0; c < 8; ++c) coef.push_back(s.coef[size_t(t) * 8 + c]);
+    // the terms of each equation (target and start) in order of their number
+    // of factors, then of their powers beyond the first (stable), the factors
+    // of a term by exponent, largest first: the tracker sweeps one term per lane,
+    // and equal shapes at equal positions keep the lanes of a wave on the same
+    // path through the sweep; the evaluation kernels are indifferent to the order
+    struct Src {
+        int sel, k, extra, first;  // first: of the factors (fv, fe)
+        const double *c;
+    };
+    std::vector<Src> src;
+    std::vector<int32_t> fv, fe;
+    auto add = [&](int sel, int k, const int32_t *var, const int32_t *exp, const double *c) {
+        int ord[32], extra = 0;
+        for (int q = 0; q < k; ++q) {
+            ord[q] = q;
+            extra += exp[q] - 1;
+        }
+        std::stable_sort(ord, ord + k, [&](int x, int y) { return exp[x] > exp[y]; });
+        src.push_back({sel, k, extra, int(fv.size()), c});
+        for (int q = 0; q < k; ++q) {
+            fv.push_back(var[ord[q]]);
+            fe.push_back(exp[ord[q]]);
         }
     };
+    auto add_system = [&](const HostSystem &s, int i, int sel) {
+        for (int t = s.eq_term_off[i]; t < s.eq_term_off[i + 1]; ++t) {
+            const int q = s.term_fac_off[t];
+            add(sel, s.term_fac_off[t + 1] - q, s.fac_var.data() + q, s.fac_exp.data() + q, &s.coef[size_t(t) * 8]);
+        }
+    };
+    static const double one[8] = {1, 0, 0, 0, 0, 0, 0, 0}, minus_one[8] = {-1, 0, 0, 0, 0, 0, 0, 0};
     for (int i = 0; i < ne; ++i) {
-        std::fill(touched.begin(), touched.end(), 0);
-        emit(f, i, 0);
+        src.clear();
+        fv.clear();
+        fe.clear();
+        add_system(f, i, 0);
         if (g) {
-            emit(*g, i, 1);
-        } else {
-            // g_i = x_i^{d_i} - 1: one term x_i^{d_i} (coefficient 1), one constant
-            // -1.  Defined for square systems only; g_i = 0 when d_i = 0.
-            int d = f.deg[i];
-            if (ne == nv && d > 0) {
-                int4 t1;
-                t1.x = 1;
-                t1.y = int(fac.size());
-                t1.z = 1;
-                t1.w = 0;
-                tdesc.push_back(t1);
-                uint32_t w = uint32_t(i) | (uint32_t(d) << 16);
-                if (!touched[i]) {
+            add_system(*g, i, 1);
+        } else if (ne == nv && f.deg[i] > 0) {
+            // g_i = x_i^{d_i} - 1, for square systems; g_i = 0 when d_i = 0
+            const int32_t v = i, d = f.deg[i];
+            add(1, 1, &v, &d, one);
+            add(1, 0, &v, &d, minus_one);
+        }
+        std::stable_sort(src.begin(), src.end(), [](const Src &x, const Src &y) {
+            return x.k != y.k ? x.k < y.k : x.extra < y.extra;
+        });
+        std::fill(touched.begin(), touched.end(), 0);
+        for (const Src &t : src) {
+            tdesc.push_back(int4{t.k, int(fac.size()), t.sel, 0});
+            kmax = std::max(kmax, t.k);
+            for (int q = t.first; q < t.first + t.k; ++q) {
+                uint32_t w = uint32_t(fv[q]) | (uint32_t(fe[q]) << 16);
+                if (!touched[fv[q]]) {
                     w |= FAC_FIRST;
-                    touched[i] = 1;
+                    touched[fv[q]] = 1;
                 }
                 fac.push_back(w);
-                double one[8] = {1, 0, 0, 0, 0, 0, 0, 0};
-                coef.insert(coef.end(), one, one + 8);
-                kmax = std::max(kmax, 1);
             }
-            if (ne == nv && d > 0) {
-                int4 t0;
-                t0.x = 0;
-                t0.y = int(fac.size());
-                t0.z = 1;
-                t0.w = 0;
-                tdesc.push_back(t0);
-                double m1[8] = {-1, 0, 0, 0, 0, 0, 0, 0};
-                coef.insert(coef.end(), m1, m1 + 8);
-            }
+            coef.insert(coef.end(), t.c, t.c + 8);
         }
         eq_off[i + 1] = int32_t(tdesc.size());
         for (int j = 0; j < nv; ++j)
@@ -263,6 +256,10 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
     for (size_t tt = 0; tt < tdesc.size(); ++tt)
         for (int l = 0; l < tdesc[tt].x && l < 8; ++l) fac8[tt * 8 + l] = fac[tdesc[tt].y + l];
 
+    // the tracker's schedule of the terms over the lanes of a whole wave
+    WideTable wide;
+    if (ne == nv && nv <= 32 && kmax <= 8) build_wide(nv, eq_off, tdesc, fac, coef, wide);
+
     size_t o_eq = 0;
     size_t o_td = o_eq + align256(eq_off.size() * 4);
     size_t o_fac = o_td + align256(tdesc.size() * sizeof(int4));
@@ -278,7 +275,12 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
     size_t o_uo = o_us + align256(u_slot.size() * 4);
     size_t o_ul = o_uo + align256(u_off.size() * 4);
     size_t o_f8 = o_ul + align256(u_list.size() * 4);
-    size_t total = o_f8 + align256(fac8.size() * 4);
+    size_t o_wm = o_f8 + align256(fac8.size() * 4);
+    size_t o_wf = o_wm + align256(wide.meta.size() * 4);
+    size_t o_wc = o_wf + align256(wide.fac.size() * 4);
+    size_t o_wh = o_wc + align256(wide.coef.size() * 8);
+    size_t o_wg = o_wh + align256(wide.chunk.size() * sizeof(int4));
+    size_t total = o_wg + align256(wide.list.size() * sizeof(uint2));
     std::vector<char> host(total, 0);
     std::memcpy(host.data() + o_eq, eq_off.data(), eq_off.size() * 4);
     std::memcpy(host.data() + o_td, tdesc.data(), tdesc.size() * sizeof(int4));
@@ -295,6 +297,13 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
     std::memcpy(host.data() + o_uo, u_off.data(), u_off.size() * 4);
     std::memcpy(host.data() + o_ul, u_list.data(), u_list.size() * 4);
     std::memcpy(host.data() + o_f8, fac8.data(), fac8.size() * 4);
+    if (wide.rounds > 0) {
+        std::memcpy(host.data() + o_wm, wide.meta.data(), wide.meta.size() * 4);
+        std::memcpy(host.data() + o_wf, wide.fac.data(), wide.fac.size() * 4);
+        std::memcpy(host.data() + o_wc, wide.coef.data(), wide.coef.size() * 8);
+        std::memcpy(host.data() + o_wh, wide.chunk.data(), wide.chunk.size() * sizeof(int4));
+        std::memcpy(host.data() + o_wg, wide.list.data(), wide.list.size() * sizeof(uint2));
+    }
     char *dev = nullptr;
     PH_HIP(hipMalloc(&dev, total));
     hipError_t e = hipMemcpy(dev, host.data(), total, hipMemcpyHostToDevice);
@@ -313,8 +322,18 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
     out.fac = reinterpret_cast<uint32_t *>(dev + o_fac);
     out.fac8 = reinterpret_cast<uint32_t *>(dev + o_f8);
     out.coef = reinterpret_cast<double *>(dev + o_cf);
+    out.wide.meta = reinterpret_cast<const uint32_t *>(dev + o_wm);
+    out.wide.fac = reinterpret_cast<const uint32_t *>(dev + o_wf);
+    out.wide.coef = reinterpret_cast<const double *>(dev + o_wc);
+    out.wide.chunk = reinterpret_cast<const int4 *>(dev + o_wh);
+    out.wide.list = reinterpret_cast<const uint2 *>(dev + o_wg);
+    out.wide.rounds = wide.rounds;
+    out.wide.chunks = int32_t(wide.chunk.size());
     out.zc_off = reinterpret_cast<int32_t *>(dev + o_zo);
     out.zc = reinterpret_cast<int32_t *>(dev + o_zc);
+    out.coef_single = true;
+    for (size_t q = 0; q < coef.size(); ++q)
+        if (q % 4 != 0 && coef[q] != 0.0) out.coef_single = false;
     out.emax = emax;
     out.dfast = dfast;
     out.dfast_planes = planes;

@@ -27,6 +27,29 @@ int track_launch(const TrackArgs &a, int prec, int kmax, int blocks, size_t lds,
     }
 }
 
+int track_wide_launch(const TrackArgs &a, int prec, int kmax, int blocks, size_t lds, hipStream_t st, int *occ)
+{
+    if (a.o.mixed) {
+        switch (prec) {
+        case 1: return track_wide_launch_t<1, true>(a, kmax, blocks, lds, st, occ);
+        case 2: return track_wide_launch_t<2, true>(a, kmax, blocks, lds, st, occ);
+        default: return track_wide_launch_t<4, true>(a, kmax, blocks, lds, st, occ);
+        }
+    }
+    switch (prec) {
+    case 1: return track_wide_launch_t<1, false>(a, kmax, blocks, lds, st, occ);
+    case 2: return track_wide_launch_t<2, false>(a, kmax, blocks, lds, st, occ);
+    default: return track_wide_launch_t<4, false>(a, kmax, blocks, lds, st, occ);
+    }
+}
+
+// the arrays of run_wide (ph_track_wide.hpp), partials for kmax factors a term
+size_t track_wide_lds_bytes(int prec, int mixed, int np_max, int kmax)
+{
+    const size_t l2 = 2 * (size_t)prec, ls2 = 2 * (size_t)(mixed ? 1 : prec), np = np_max;
+    return (np * l2 + (np + 1) * np * ls2 + np * ls2 + 64 * (size_t)WIDE_ROUNDS * (l2 + kmax * ls2)) * sizeof(double);
+}
+
 size_t track_lds_bytes(int prec, int mixed, int np_max)
 {
     const int ls = mixed ? 1 : prec;
@@ -179,21 +202,36 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
     int dev = 0, cus = 256;
     PH_HIP(hipGetDevice(&dev));
     PH_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // lanes per path: as asked, else the natural count, doubled when the
-    // paths at their natural count fill less than one wave per SIMD (the
-    // extra lanes share each equation's term sweeps; results are unchanged)
+    // lanes per path: as asked; else a whole wave while the paths are few (a run
+    // lasts as long as its longest path, and a wave takes a path's Newton
+    // iteration in a quarter of the time); else the natural count, where a
+    // wave's lanes do less in vain.  The line lies where the two took equal
+    // time, at this many paths per resident wave (2048 of them): n = 3 between
+    // one quarter (512 paths: 1.15 ms against 0.80 ms) and two (4096: 1.09 /
+    // 1.70); n = 8 between 3 (6561 paths: 91 / 43 ms in double double, 57 / 31
+    // in double) and 26 (52488: 132 / 185); n = 16 near 12 (24576 paths: 515 /
+    // 483 ms in quad double, 157 / 172 in double; 65536: 1028 / 1232).
     int lanes_pp = opts->lanes_per_path;
+    bool wide = false;
     if (lanes_pp == 0) {
-        double lanes = 0;
+        const double waves = 8.0 * cus;
+        double lanes = 0, share = 0;
         int nat_max = 4;
         for (int s = 0; s < nsys; ++s) {
             if (!targets[s]) return fail(PH_EINVAL, "null target system");
             int nat = 4;
             while (nat < targets[s]->h.n_var) nat *= 2;
             nat_max = std::max(nat_max, nat);
-            lanes += (double)(path_off[s + 1] - path_off[s]) * nat;
+            const double np = (double)(path_off[s + 1] - path_off[s]);
+            lanes += np * nat;
+            share += np / (waves * (nat <= 4 ? 1 : (nat <= 8 ? 8 : 11)));
         }
-        if (lanes < 64.0 * 4 * cus && 2 * nat_max <= 32) lanes_pp = 2 * nat_max;
+        // the history of the no-allocation scratch is bounded for the lanes of
+        // the other kernel
+        wide = share <= 1.0 && !(noalloc && opts->predictor_order > 1);
+        // where a wave per path is ruled out: twice the natural count when
+        // the paths fill less than one wave per SIMD
+        if (!wide && lanes < 64.0 * 4 * cus && 2 * nat_max <= 32) lanes_pp = 2 * nat_max;
     }
 
     // ---- systems grouped by lane-count class (4, 8, 16, 32 lanes per path)
@@ -201,6 +239,7 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
     desc.reserve(nsys);
     TrackArgs a;
     std::memset(&a, 0, sizeof a);
+    a.coef_single = 1;
     int kmax = 1, np_max = 4;
     const int class_np[4] = {4, 8, 16, 32};
     double work[4] = {0, 0, 0, 0};
@@ -227,6 +266,7 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
             d.fac = tab->fac;
             d.fac8 = tab->fac8;
             d.coef = tab->coef;
+            d.wide = tab->wide;
             d.path_off = path_off[s];
             d.npaths = path_off[s + 1] - path_off[s];
             d.qoff = q;
@@ -263,8 +303,11 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
                 }
             }
             kmax = std::max(kmax, tab->kmax);
-            // work estimate: lanes times terms per equation
-            work[c] += (double)d.npaths * class_np[c] * (double)tab->n_terms / std::max(1, n);
+            if (!tab->coef_single) a.coef_single = 0;
+            // work estimate: lanes times terms per equation (a wave per path:
+            // rounds of terms and steps of the solve)
+            work[c] += wide ? (double)d.npaths * (tab->wide.rounds + 0.25 * n)
+                            : (double)d.npaths * class_np[c] * (double)tab->n_terms / std::max(1, n);
             desc.push_back(d);
         }
         a.cls[c].sys_end = (int)desc.size();
@@ -325,11 +368,16 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
     // no more workgroups than fit the CUs at once, so that every workgroup of
     // a launch starts with it (a round launch whose last workgroups waited
     // for the first ones to end would run twice its budget, mostly idle)
-    const size_t lds = track_lds_bytes(prec, opts->mixed, np_max);
+    const size_t lds = wide ? track_wide_lds_bytes(prec, opts->mixed, np_max, kmax)
+                            : track_lds_bytes(prec, opts->mixed, np_max);
+    auto launch = [&](int nblocks, hipStream_t s, int *occ) {
+        return wide ? track_wide_launch(a, prec, kmax, nblocks, lds, s, occ)
+                    : track_launch(a, prec, kmax, nblocks, lds, s, occ);
+    };
     int per_cu = opts->blocks_per_cu > 0 ? opts->blocks_per_cu : 8;
     {
         int occ = 0;
-        rc = track_launch(a, prec, kmax, 0, lds, st, &occ);
+        rc = launch(0, st, &occ);
         if (rc) return rc;
         if (occ > 0) per_cu = std::min(per_cu, occ);
     }
@@ -346,7 +394,8 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
     int blocks = 0;
     for (int c = 0; c < 4; ++c) {
         if (a.cls[c].total > 0) {
-            const int64_t need = (a.cls[c].total + (64 / class_np[c]) - 1) / (64 / class_np[c]);
+            const int per_wave = wide ? 1 : 64 / class_np[c];
+            const int64_t need = (a.cls[c].total + per_wave - 1) / per_wave;
             nbc[c] = (int)std::max<int64_t>(1, std::min<int64_t>(need, (int64_t)std::floor(cap * work[c] / wsum)));
         }
         blocks += nbc[c];
@@ -366,8 +415,10 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
         a.cls[c].block_end = blocks;
     }
     if (opts->predictor_order > 1) {
-        // three older points per lane slot, kept across launches
-        a.hist_ld = (int64_t)blocks * 64;
+        // three older points per lane slot (a wave per path: per row of the
+        // path), kept across launches
+        a.wide_cols = np_max;
+        a.hist_ld = (int64_t)blocks * (wide ? np_max : 64);
         const size_t hist_bytes = sizeof(double) * 3 * 2 * prec * (size_t)a.hist_ld;
         if (noalloc) {
             if (hist_bytes > NOALLOC_BYTES - NOALLOC_HIST_OFF) {
@@ -416,7 +467,7 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
         hipGraphExec_t exec = nullptr;
         PH_HIP(hipStreamBeginCapture(cs.s, hipStreamCaptureModeThreadLocal));
         int rc1 = clear_counter_launch(a.active, cs.s);
-        int rc2 = rc1 ? rc1 : track_launch(a, prec, kmax, blocks, lds, cs.s);
+        int rc2 = rc1 ? rc1 : launch(blocks, cs.s, nullptr);
         hipError_t ec = hipStreamEndCapture(cs.s, &graph);
         if (rc2) {
             if (graph) (void)hipGraphDestroy(graph);
@@ -458,7 +509,7 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
         if (active > 0) return fail(PH_EHIP, "graph schedule did not drain the work queue");
     } else {
         a.state = nullptr;
-        rc = track_launch(a, prec, kmax, blocks, lds, st);
+        rc = launch(blocks, st, nullptr);
         if (rc) return rc;
     }
     unsigned long long h[16];
