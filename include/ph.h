@@ -156,7 +156,11 @@ int ph_eval_prepare(ph_system *target, const ph_system *start, int32_t prec,
  * device memory between them; an ablation of the fused kernels, whose
  * intermediate arrays ph_eval_prepare sizes; waves and groups are ignored);
  * kernels 2, 3 and 4 produce the Jacobian: a values-only call (jac NULL)
- * runs the general kernel with the same waves and groups;
+ * runs the general kernel with the same waves and groups, or, in double double
+ * and quad double under kernels 0 and 3 where the fast path applies, a kernel
+ * of its own with its own tiling;
+ * the automatic choice also takes the fast path for terms of 9 to 16 factors
+ * of exponent 1, which kernels 3 and 4 refuse;
  * waves = waves per workgroup sharing one 64-point tile (1..8, 0 default;
  * taken as given, so counts like 6 can match the register budget);
  * groups = equation groups per tile (power of two, 0 default).  All zero

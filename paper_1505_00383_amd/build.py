@@ -65,13 +65,16 @@ def kept_asm(src: str) -> str | None:
 # parallel.
 TRACK_UNITS = {"track_unit.hip": "track", "track_wide_unit.hip": "track_wide"}
 TRACK_VARIANTS = [(L, m) for L in (1, 2, 4) for m in (1, 0)]
+# The fast-path kernel with records of long terms is a second compilation of the
+# same source.
+LONG_UNITS = ("eval.hip", "eval_dd.hip", "eval_qd.hip")
 
 
 def sources():
     """(source, object name, extra flags) of every compilation."""
     out = []
     # the heaviest compilations first: the tracker units, then eval.hip
-    for f in sorted(os.listdir(CSRC), key=lambda f: (f not in TRACK_UNITS, f != "eval.hip", f)):
+    for f in sorted(os.listdir(CSRC), key=lambda f: (f not in TRACK_UNITS, f not in LONG_UNITS, f)):
         if not f.endswith((".hip", ".cpp")):
             continue
         if f in TRACK_UNITS:
@@ -80,6 +83,8 @@ def sources():
                             [f"-DPH_TRACK_L={L}", f"-DPH_TRACK_MIXED={m}"]))
         else:
             out.append((f, f + ".o", []))
+            if f in LONG_UNITS:
+                out.append((f, f + ".long.o", ["-DPH_LONG_UNIT"]))
     return out
 
 
@@ -87,7 +92,7 @@ def _compile(job) -> str:
     src, oname, extra = job
     obj = os.path.join(BUILD, oname)
     lang = ["-x", "hip"] if src.endswith(".hip") else []
-    keep = ["-save-temps=obj"] if src in ASM_KEPT else []
+    keep = ["-save-temps=obj"] if src in ASM_KEPT and not extra else []
     fp = asm_fingerprint(src) if keep else None
     cmd = [HIPCC] + lang + COMMON + DEVICE + extra + keep + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True, cwd=BUILD)

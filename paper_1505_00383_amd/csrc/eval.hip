@@ -516,7 +516,7 @@ __device__ __forceinline__ DHead dfast_head(const DTerm *__restrict__ r)
 // of the K - M factors with exponent 1 are fused into their row updates).
 // A term's factors are distinct unknowns, so the order of its row updates
 // does not change any result.
-template <int K, int M, class Row>
+template <int K, int M, bool LONG, class Row>
 __device__ __forceinline__ void dfast_sweep(const DHead &h, const DTerm *__restrict__ rnext, DHead &hnext,
                                             const char *__restrict__ xb, int lane, C<1> cf,
                                             Row &row, C<1> &v)
@@ -556,13 +556,13 @@ __device__ __forceinline__ void dfast_sweep(const DHead &h, const DTerm *__restr
         }
         q = c_mul<1>(q, xv[l]);
     }
-    v = c_add<1>(v, c_mul<1>(q, xv[K - 1]));
+    if (!LONG || K < 5 || !(h.sel & DSEL_NOVALUE)) v = c_add<1>(v, c_mul<1>(q, xv[K - 1]));
     row.fma((int)h.j2[K - 1], h.a[K - 1], q);
 }
 
 // All records of one equation, group by group: (K, M) = (1,0), (1,1), (2,0),
 // ..., (8,8), each a straight-line loop over its records.
-template <int K, int M, int KF, class Row>
+template <int K, int M, int KF, bool LONG, class Row>
 __device__ __forceinline__ void dfast_groups(const int32_t *__restrict__ run, const DTerm *__restrict__ dterm,
                                              const char *__restrict__ xb, int lane, const C<1> &gs,
                                              double tv, Row &row, C<1> &v)
@@ -576,19 +576,19 @@ __device__ __forceinline__ void dfast_groups(const int32_t *__restrict__ run, co
             const C<1> c0 = c_from<1>(h.cre, h.cim);
             const C<1> c = (h.sel & 1) ? c_mul<1>(c0, gs) : c_mul_d<1>(c0, tv);
             DHead hn;
-            dfast_sweep<K, M>(h, rn, hn, xb, lane, c, row, v);
+            dfast_sweep<K, M, LONG>(h, rn, hn, xb, lane, c, row, v);
             h = hn;
         }
     }
     if constexpr (M < K)
-        dfast_groups<K, M + 1, KF>(run, dterm, xb, lane, gs, tv, row, v);
+        dfast_groups<K, M + 1, KF, LONG>(run, dterm, xb, lane, gs, tv, row, v);
     else if constexpr (K < KF)
-        dfast_groups<K + 1, 0, KF>(run, dterm, xb, lane, gs, tv, row, v);
+        dfast_groups<K + 1, 0, KF, LONG>(run, dterm, xb, lane, gs, tv, row, v);
 }
 
 // KF: largest number of factors per term the kernel handles; NC: largest
 // number of unknowns (Jacobian columns held in the row).
-template <class Row, int KF, int NC>
+template <class Row, int KF, int NC, bool LONG = false>
 __device__ __forceinline__ void dfast_body(const EvalArgs &a, const int32_t *__restrict__ d_run,
                                            const DTerm *__restrict__ dterm,
                                            const int32_t *__restrict__ d_deg, int planes)
@@ -633,7 +633,7 @@ __device__ __forceinline__ void dfast_body(const EvalArgs &a, const int32_t *__r
             return (r->sel & 1) ? c_mul<1>(c, gs) : c_mul_d<1>(c, tv);
         };
         for (int s = run[0]; s < run[1]; ++s) v = c_add<1>(v, coef(dterm + s));
-        dfast_groups<1, 0, KF>(run, dterm, xb, lane, gs, tv, row, v);
+        dfast_groups<1, 0, KF, LONG>(run, dterm, xb, lane, gs, tv, row, v);
         // total-degree start part: gamma (1-t) (x_i^d - 1), derivative d x_i^(d-1)
         const int d = d_deg[i];
         if (d > 0 && a.t) {
@@ -677,6 +677,32 @@ __device__ __forceinline__ void dfast_body(const EvalArgs &a, const int32_t *__r
         }
     }
 }
+
+// Launch of eval_d_pinned_long_kernel, which is compiled by itself
+// (-DPH_LONG_UNIT).
+void d_long_launch(dim3 grid, dim3 block, size_t lds, hipStream_t st, const EvalArgs &a, const int32_t *d_run,
+                   const DTerm *dterm, const int32_t *d_deg, int planes);
+
+#ifdef PH_LONG_UNIT
+
+// eval_d_pinned_kernel with records that add no value (terms of more than 8
+// factors) among them.
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_num_vgpr(128)))
+eval_d_pinned_long_kernel(EvalArgs a, const int32_t *__restrict__ d_run, const DTerm *__restrict__ dterm,
+                          const int32_t *__restrict__ d_deg, int planes)
+{
+    dfast_body<PinRow, 8, 32, true>(a, d_run, dterm, d_deg, planes);
+}
+
+void d_long_launch(dim3 grid, dim3 block, size_t lds, hipStream_t st, const EvalArgs &a, const int32_t *d_run,
+                   const DTerm *dterm, const int32_t *d_deg, int planes)
+{
+    hipLaunchKernelGGL(eval_d_pinned_long_kernel, grid, block, lds, st, a, d_run, dterm, d_deg, planes);
+}
+
+}  // namespace ph
+
+#else
 
 __global__ void __launch_bounds__(512) eval_d_fast_kernel(EvalArgs a, const int32_t *__restrict__ d_run,
                                                           const DTerm *__restrict__ dterm,
@@ -766,21 +792,26 @@ int eval_launch(const DevTable &tab, const double gamma[2], int prec, int64_t np
     const bool can_reg = prec == 1 && wj && tab.n_var <= 32 && tab.kmax <= 16;
     int kernel = cfg ? cfg->kernel : 0;
     if (kernel == 5) return unfused_launch(tab, gamma, prec, npts, t, x, ld, val, jac, st);
-    // the register-row kernels produce the Jacobian; values alone take the
-    // general kernel with the same tiling
+    // values alone: a kernel of the records' chains of products in double
+    // double and quad double, else the general kernel (the register-row kernels
+    // produce the Jacobian)
+    if (!wj && (kernel == 0 || kernel == 3) && prec > 1 && tab.n_var <= 32 && tab.dfast && tab.mfast)
+        return prec == 4 ? qd_values_launch(tab, gamma, npts, t, x, ld, val, st)
+                         : dd_values_launch(tab, gamma, npts, t, x, ld, val, st);
     if (!wj && kernel >= 2) kernel = 1;
-    if ((kernel == 3 || kernel == 4) && !can_fast)
+    // (terms of more than 8 factors: by the automatic choice only)
+    if ((kernel == 3 || kernel == 4) && (!can_fast || tab.dlong))
         return fail(PH_EUNSUPPORTED, "fast path not available for this system");
     if (kernel == 4 && prec != 1)
         return fail(PH_EUNSUPPORTED, "the compiler-held row is a complex-double kernel");
     if (kernel == 2 && !can_reg) return fail(PH_EUNSUPPORTED, "register-row kernel not available");
     if (kernel == 0) kernel = can_fast ? 3 : (can_reg ? 2 : 1);
     if (kernel == 3 && prec == 2)
-        return dd_fast_launch(tab, gamma, npts, t, x, ld, val, jac, cfg && cfg->W > 0 ? cfg->W : 4,
-                              cfg && cfg->G > 0 ? cfg->G : 1, st);
+        return dd_fast_launch(tab, gamma, npts, t, x, ld, val, jac, cfg && cfg->W > 0 ? cfg->W : 0,
+                              cfg && cfg->G > 0 ? cfg->G : 0, st);
     if (kernel == 3 && prec == 4)
-        return qd_fast_launch(tab, gamma, npts, t, x, ld, val, jac, cfg && cfg->W > 0 ? cfg->W : 4,
-                              cfg && cfg->G > 0 ? cfg->G : 1, st);
+        return qd_fast_launch(tab, gamma, npts, t, x, ld, val, jac, cfg && cfg->W > 0 ? cfg->W : 0,
+                              cfg && cfg->G > 0 ? cfg->G : 0, st);
     if ((kernel == 3 || kernel == 4) && prec != 1)
         return fail(PH_EUNSUPPORTED, "fast path not available at this precision");
     // waves per workgroup: all of them share the 64 points staged in LDS and
@@ -803,14 +834,25 @@ int eval_launch(const DevTable &tab, const double gamma[2], int prec, int64_t np
     } else {
         while (blocks * G < 1024 && G * W * 2 <= tab.n_eq) G *= 2;
     }
+    const size_t ldsf = ((size_t)tab.dfast_planes * tab.n_var * 2 + 2) * 64 * sizeof(double);
+    const bool pin16 = kernel == 3 && tab.n_var <= 16 && tab.kmax <= 2;
+    if (kernel == 3 && !pin16 && !(cfg && cfg->W > 0 && cfg->G > 0)) {
+        // two waves per SIMD; staging: about sixty products' time.  (The
+        // 16-column kernel is bound by what it writes and keeps the counts
+        // above: 0.86 ms for 2^20 points of n = 16, 0.91 ms by this choice.)
+        const EvalFit ft = eval_fit(tab, blocks, 8, cfg && cfg->W > 0 ? W : 0, 8, ldsf, 60.0, 1.11);
+        if (!(cfg && cfg->W > 0)) W = ft.W;
+        if (!(cfg && cfg->G > 0)) G = ft.G;
+    }
     a.eq_stride = G * W;
     dim3 grid((unsigned)blocks, (unsigned)G);
     const size_t lds = (size_t)tab.n_var * 2 * prec * 64 * sizeof(double);
     if (kernel == 3 || kernel == 4) {
-        const size_t ldsf = ((size_t)tab.dfast_planes * tab.n_var * 2 + 2) * 64 * sizeof(double);
-        if (kernel == 3 && tab.n_var <= 16 && tab.kmax <= 2)
+        if (pin16)
             hipLaunchKernelGGL(eval_d_pinned16_kernel, grid, dim3(64 * W), ldsf, st, a, tab.d_run,
                                tab.dterm, tab.d_deg, tab.dfast_planes);
+        else if (kernel == 3 && tab.dlong)
+            d_long_launch(grid, dim3(64 * W), ldsf, st, a, tab.d_run, tab.dterm, tab.d_deg, tab.dfast_planes);
         else if (kernel == 3)
             hipLaunchKernelGGL(eval_d_pinned_kernel, grid, dim3(64 * W), ldsf, st, a, tab.d_run,
                                tab.dterm, tab.d_deg, tab.dfast_planes);
@@ -957,8 +999,10 @@ extern "C" int ph_eval_autotune(ph_system *target, const ph_system *start, const
     PH_HIP(hipEventCreate(&e1));
     EvalCfg best;
     double best_t = 1e300;
-    const int kernels[4] = {3, 4, 2, 1};
+    // the automatic choice where it is a kernel that cannot be asked for
+    const int kernels[5] = {3, 4, 2, 1, 0};
     for (int kk : kernels) {
+        if (kk == 0 && !tab->dlong) continue;
         for (int W : {1, 2, 4, 6, 8}) {
             for (int G = 1; G <= 8; G *= 2) {
                 if (W * G > tab->n_eq) continue;
@@ -1003,3 +1047,5 @@ done:
     (void)hipEventDestroy(e1);
     return rc;
 }
+
+#endif  // PH_LONG_UNIT

@@ -95,7 +95,7 @@ __device__ __forceinline__ C<2> lds2(const char *__restrict__ xb, uint32_t off, 
 
 // One term with K factors, the first M of them with a >= 2 (same product
 // order as the complex-double fast path).
-template <int K, int M>
+template <int K, int M, bool LONG>
 __device__ __forceinline__ void mfast_sweep(const MHead<2> &h, const MTerm *__restrict__ rnext, MHead<2> &hnext,
                                             const char *__restrict__ xb, int lane, C<2> cf, ARow &row,
                                             C<2> &v)
@@ -124,7 +124,7 @@ __device__ __forceinline__ void mfast_sweep(const MHead<2> &h, const MTerm *__re
         q = c_mul<2>(q, xv[l]);
         row_axpy(row, h.jo[l], h.a[l], part);
     }
-    val_acc(v, c_mul<2>(q, xv[K - 1]));
+    if (!LONG || K < 5 || !(h.sel & DSEL_NOVALUE)) val_acc(v, c_mul<2>(q, xv[K - 1]));
     row_axpy(row, h.jo[K - 1], h.a[K - 1], q);
 }
 
@@ -138,7 +138,7 @@ __device__ __forceinline__ C<2> mcoef(const MHead<2> &h, const C<2> &gs, double 
     return (h.sel & 1) ? c_mul<2>(c, gs) : c_mul_d<2>(c, tv);
 }
 
-template <int K, int M, int KF>
+template <int K, int M, int KF, bool LONG>
 __device__ __forceinline__ void mfast_groups(const int32_t *__restrict__ run, const MTerm *__restrict__ mt,
                                              const char *__restrict__ xb, int lane, const C<2> &gs,
                                              double tv, ARow &row, C<2> &v)
@@ -150,22 +150,23 @@ __device__ __forceinline__ void mfast_groups(const int32_t *__restrict__ run, co
         for (int s = s0; s < s1; ++s) {
             const MTerm *rn = mt + (s + 1 < s1 ? s + 1 : s);
             MHead<2> hn;
-            mfast_sweep<K, M>(h, rn, hn, xb, lane, mcoef(h, gs, tv), row, v);
+            mfast_sweep<K, M, LONG>(h, rn, hn, xb, lane, mcoef(h, gs, tv), row, v);
             h = hn;
         }
     }
     if constexpr (M < K)
-        mfast_groups<K, M + 1, KF>(run, mt, xb, lane, gs, tv, row, v);
+        mfast_groups<K, M + 1, KF, LONG>(run, mt, xb, lane, gs, tv, row, v);
     else if constexpr (K < KF)
-        mfast_groups<K + 1, 0, KF>(run, mt, xb, lane, gs, tv, row, v);
+        mfast_groups<K + 1, 0, KF, LONG>(run, mt, xb, lane, gs, tv, row, v);
 }
 
 __device__ __forceinline__ void st_nt(double *p, double v) { __builtin_nontemporal_store(v, p); }
 
 // One wave per SIMD: 256 architectural registers for the sweep, 256 AGPRs
 // for the row (at most four waves per workgroup).
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-eval_dd_arow_kernel(DDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
+// LONG: records without a value (terms of more than 8 factors) among them.
+template <bool LONG>
+__device__ __forceinline__ void eval_dd_arow_body(DDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
                     const int32_t *__restrict__ d_deg)
 {
     extern __shared__ double xl[];
@@ -228,7 +229,7 @@ eval_dd_arow_kernel(DDArgs a, const int32_t *__restrict__ d_run, const MTerm *__
             MHead<2> h = mfast_head<0, 0, 2>(mterm + s);
             val_acc(v, mcoef(h, gs, tv));
         }
-        mfast_groups<1, 0, 8>(run, mterm, xb, lane, gs, tv, row, v);
+        mfast_groups<1, 0, 8, LONG>(run, mterm, xb, lane, gs, tv, row, v);
         // total-degree start part: gamma (1-t) (x_i^d - 1), derivative d x_i^(d-1)
         const int d = d_deg[i];
         if (d > 0 && a.t) {
@@ -262,6 +263,34 @@ eval_dd_arow_kernel(DDArgs a, const int32_t *__restrict__ d_run, const MTerm *__
     }
 }
 
+// Launch of the kernel with LONG, which is compiled by itself (-DPH_LONG_UNIT).
+void dd_long_launch(dim3 grid, dim3 block, size_t lds, hipStream_t st, const DDArgs &a, const int32_t *d_run,
+                    const MTerm *mterm, const int32_t *d_deg);
+
+#ifdef PH_LONG_UNIT
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+eval_dd_arow_long_kernel(DDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
+                    const int32_t *__restrict__ d_deg)
+{
+    eval_dd_arow_body<true>(a, d_run, mterm, d_deg);
+}
+
+void dd_long_launch(dim3 grid, dim3 block, size_t lds, hipStream_t st, const DDArgs &a, const int32_t *d_run,
+                    const MTerm *mterm, const int32_t *d_deg)
+{
+    hipLaunchKernelGGL(eval_dd_arow_long_kernel, grid, block, lds, st, a, d_run, mterm, d_deg);
+}
+
+#else
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+eval_dd_arow_kernel(DDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
+                    const int32_t *__restrict__ d_deg)
+{
+    eval_dd_arow_body<false>(a, d_run, mterm, d_deg);
+}
+
 int dd_fast_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t,
                    const double *x, int64_t ld, double *val, double *jac, int W, int G,
                    hipStream_t st)
@@ -278,17 +307,29 @@ int dd_fast_launch(const DevTable &tab, const double gamma[2], int64_t npts, con
     a.n_eq = tab.n_eq;
     a.n_var = tab.n_var;
     a.planes = tab.dfast_planes;
-    W = W < 1 ? 1 : (W > 4 ? 4 : W);
-    if (W > tab.n_eq) W = tab.n_eq;
-    if (G < 1) G = 1;
-    while (G > 1 && G * W > tab.n_eq) G >>= 1;
-    a.eq_stride = G * W;
     const size_t lds = ((size_t)tab.dfast_planes * tab.n_var * 4 + 4) * 64 * sizeof(double);
+    // one wave per SIMD, at most four waves per workgroup; staging: about twenty
+    // products' time to read the points, and a product per power
+    if (W > 4) W = 4;
+    if (W > tab.n_eq) W = tab.n_eq;
+    if (W < 1 || G < 1) {
+        const EvalFit ft = eval_fit(tab, (npts + 63) / 64, 4, W, 4, lds, 20.0, 1.0);
+        if (W < 1) W = ft.W;
+        if (G < 1) G = ft.G;
+    } else {
+        while (G > 1 && G * W > tab.n_eq) G >>= 1;
+    }
+    a.eq_stride = G * W;
     dim3 grid((unsigned)((npts + 63) / 64), (unsigned)G);
-    hipLaunchKernelGGL(eval_dd_arow_kernel, grid, dim3(64 * W), lds, st, a, tab.d_run, tab.mterm, tab.d_deg);
+    if (tab.dlong)
+        dd_long_launch(grid, dim3(64 * W), lds, st, a, tab.d_run, tab.mterm, tab.d_deg);
+    else
+        hipLaunchKernelGGL(eval_dd_arow_kernel, grid, dim3(64 * W), lds, st, a, tab.d_run, tab.mterm, tab.d_deg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "eval_dd_arow_kernel launch");
     return PH_OK;
 }
+
+#endif
 
 }  // namespace ph

@@ -159,10 +159,63 @@ __device__ __forceinline__ R<4> qcoef(const MHead<4> &h, const QLane &ql)
     return r_mul_d<4>(own, ql.tv);  // t c
 }
 
+// Stage the tile's coordinates and powers, and the point's c(t).
+__device__ __forceinline__ void qd_stage(const QDArgs &a, double *__restrict__ xl, int64_t P, bool act, int w, int W,
+                                         QLane &ql, C<4> &gs)
+{
+    const int nv = a.n_var;
+    // stage x and its powers (each lane writes its component's four rows)
+    for (int var = w; var < nv; var += W) {
+        C<4> x1 = c_zero<4>();
+        if (act) {
+#pragma unroll
+            for (int l = 0; l < 4; ++l) {
+                x1.re.v[l] = a.x[(int64_t)(var * 8 + l) * a.ld + P];
+                x1.im.v[l] = a.x[(int64_t)(var * 8 + 4 + l) * a.ld + P];
+            }
+        }
+        C<4> z = x1;
+        for (int q = 0; q < a.planes; ++q) {
+            double *row = xl + (size_t)((q * nv + var) * 8 + 4 * ql.c) * 32 + ql.p;
+            const R<4> own = ql.c ? z.im : z.re;
+#pragma unroll
+            for (int l = 0; l < 4; ++l) row[l * 32] = own.v[l];
+            if (q + 1 < a.planes) z = c_mul<4>(z, x1);
+        }
+    }
+    if (w == 0) {
+        double *row = xl + (size_t)(a.planes * nv * 8 + 4 * ql.c) * 32 + ql.p;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) row[l * 32] = (ql.c == 0 && l == 0) ? 1.0 : 0.0;
+    }
+    __syncthreads();
+
+    // c(t): t for target terms, gamma (1 - t) for start terms, (1 - t) exact
+    ql.tv = 1.0;
+    if (a.t) ql.tv = act ? a.t[P] : 0.0;
+    gs = c_zero<4>();
+    if (a.t) {
+        double o, oe;
+        two_sum(1.0, -ql.tv, o, oe);
+        R<4> omt = r_zero<4>();
+        omt.v[0] = o;
+        omt.v[1] = oe;
+        gs = c_mul_r<4>(c_from<4>(a.gre, a.gim), omt);
+    }
+    ql.gs_own = ql.c ? gs.im : gs.re;
+    {
+        const R<4> oth = ql.c ? gs.re : gs.im;
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            ql.gs_oth_s.v[l] = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, oth.v[l]) ^
+                                                              ((unsigned long long)ql.sg << 32));
+    }
+}
+
 // One term with K factors, the first M of them with a >= 2.
 // (A quad-double term takes thousands of instructions, so its record is
 // simply read at its start: the scalar loads are not on the critical path.)
-template <int K, int M>
+template <int K, int M, bool LONG>
 __device__ __forceinline__ void qfast_sweep(const MHead<4> &h, const char *__restrict__ xb, const QLane &ql,
                                             R<4> cf, ARow &row, R<4> &v)
 {
@@ -201,11 +254,12 @@ __device__ __forceinline__ void qfast_sweep(const MHead<4> &h, const char *__res
         q = pmul(q, qo, lds_nat(xb, h.xo[l], ql.p));
         qrow_axpy(row, h.jo[l], h.a[l], part);
     }
-    v = r_add<4>(v, pmul(q, other_signed(q, ql.sg), lds_nat(xb, h.xo[K - 1], ql.p)));
+    if (!LONG || K < 5 || !(h.sel & DSEL_NOVALUE))
+        v = r_add<4>(v, pmul(q, other_signed(q, ql.sg), lds_nat(xb, h.xo[K - 1], ql.p)));
     qrow_axpy(row, h.jo[K - 1], h.a[K - 1], q);
 }
 
-template <int K, int M, int KF>
+template <int K, int M, int KF, bool LONG>
 __device__ __forceinline__ void qfast_groups(const int32_t *__restrict__ run, const MTerm *__restrict__ mt,
                                              const char *__restrict__ xb, const QLane &ql, ARow &row, R<4> &v)
 {
@@ -213,20 +267,21 @@ __device__ __forceinline__ void qfast_groups(const int32_t *__restrict__ run, co
     const int s0 = run[g], s1 = run[g + 1];
     for (int s = s0; s < s1; ++s) {
         const MHead<4> h = mfast_head<K, M, 4>(mt + s);
-        qfast_sweep<K, M>(h, xb, ql, qcoef(h, ql), row, v);
+        qfast_sweep<K, M, LONG>(h, xb, ql, qcoef(h, ql), row, v);
     }
     if constexpr (M < K)
-        qfast_groups<K, M + 1, KF>(run, mt, xb, ql, row, v);
+        qfast_groups<K, M + 1, KF, LONG>(run, mt, xb, ql, row, v);
     else if constexpr (K < KF)
-        qfast_groups<K + 1, 0, KF>(run, mt, xb, ql, row, v);
+        qfast_groups<K + 1, 0, KF, LONG>(run, mt, xb, ql, row, v);
 }
 
 __device__ __forceinline__ void st_nt4(double *p, double v) { __builtin_nontemporal_store(v, p); }
 
 // One wave per SIMD (256 architectural registers for the sweep, 256 AGPRs
 // for the row component); at most four waves per workgroup.
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
-eval_qd_arow_kernel(QDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
+// LONG: records without a value (terms of more than 8 factors) among them.
+template <bool LONG>
+__device__ __forceinline__ void eval_qd_arow_body(QDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
                     const int32_t *__restrict__ d_deg)
 {
     extern __shared__ double xl[];
@@ -241,52 +296,8 @@ eval_qd_arow_kernel(QDArgs a, const int32_t *__restrict__ d_run, const MTerm *__
     const int64_t P = (int64_t)blockIdx.x * 32 + ql.p;
     const bool act = P < a.npts;
     const int nv = a.n_var;
-    // stage x and its powers (each lane writes its component's four rows)
-    for (int var = w; var < nv; var += W) {
-        C<4> x1 = c_zero<4>();
-        if (act) {
-#pragma unroll
-            for (int l = 0; l < 4; ++l) {
-                x1.re.v[l] = a.x[(int64_t)(var * 8 + l) * a.ld + P];
-                x1.im.v[l] = a.x[(int64_t)(var * 8 + 4 + l) * a.ld + P];
-            }
-        }
-        C<4> z = x1;
-        for (int q = 0; q < a.planes; ++q) {
-            double *row = xl + (size_t)((q * nv + var) * 8 + 4 * ql.c) * 32 + ql.p;
-            const R<4> own = ql.c ? z.im : z.re;
-#pragma unroll
-            for (int l = 0; l < 4; ++l) row[l * 32] = own.v[l];
-            if (q + 1 < a.planes) z = c_mul<4>(z, x1);
-        }
-    }
-    if (w == 0) {
-        double *row = xl + (size_t)(a.planes * nv * 8 + 4 * ql.c) * 32 + ql.p;
-#pragma unroll
-        for (int l = 0; l < 4; ++l) row[l * 32] = (ql.c == 0 && l == 0) ? 1.0 : 0.0;
-    }
-    __syncthreads();
-
-    // c(t): t for target terms, gamma (1 - t) for start terms, (1 - t) exact
-    ql.tv = 1.0;
-    if (a.t) ql.tv = act ? a.t[P] : 0.0;
-    C<4> gs = c_zero<4>();
-    if (a.t) {
-        double o, oe;
-        two_sum(1.0, -ql.tv, o, oe);
-        R<4> omt = r_zero<4>();
-        omt.v[0] = o;
-        omt.v[1] = oe;
-        gs = c_mul_r<4>(c_from<4>(a.gre, a.gim), omt);
-    }
-    ql.gs_own = ql.c ? gs.im : gs.re;
-    {
-        const R<4> oth = ql.c ? gs.re : gs.im;
-#pragma unroll
-        for (int l = 0; l < 4; ++l)
-            ql.gs_oth_s.v[l] = __builtin_bit_cast(double, __builtin_bit_cast(unsigned long long, oth.v[l]) ^
-                                                              ((unsigned long long)ql.sg << 32));
-    }
+    C<4> gs;
+    qd_stage(a, xl, P, act, w, W, ql, gs);
 
     for (int i = blockIdx.y * W + w; i < a.n_eq; i += a.eq_stride) {
         ARow row;
@@ -294,7 +305,7 @@ eval_qd_arow_kernel(QDArgs a, const int32_t *__restrict__ d_run, const MTerm *__
         R<4> v = r_zero<4>();
         const int32_t *run = d_run + i * DRUN;
         for (int s = run[0]; s < run[1]; ++s) v = r_add<4>(v, qcoef(mfast_head<0, 0, 4>(mterm + s), ql));
-        qfast_groups<1, 0, 8>(run, mterm, xb, ql, row, v);
+        qfast_groups<1, 0, 8, LONG>(run, mterm, xb, ql, row, v);
         // total-degree start part: gamma (1-t) (x_i^d - 1), derivative d x_i^(d-1)
         // (whole complex values in both lanes, then the own component)
         const int d = d_deg[i];
@@ -326,6 +337,120 @@ eval_qd_arow_kernel(QDArgs a, const int32_t *__restrict__ d_run, const MTerm *__
     }
 }
 
+// Launch of the kernel with LONG, which is compiled by itself (-DPH_LONG_UNIT).
+void qd_long_launch(dim3 grid, dim3 block, size_t lds, hipStream_t st, const QDArgs &a, const int32_t *d_run,
+                    const MTerm *mterm, const int32_t *d_deg);
+
+#ifdef PH_LONG_UNIT
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+eval_qd_arow_long_kernel(QDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
+                    const int32_t *__restrict__ d_deg)
+{
+    eval_qd_arow_body<true>(a, d_run, mterm, d_deg);
+}
+
+void qd_long_launch(dim3 grid, dim3 block, size_t lds, hipStream_t st, const QDArgs &a, const int32_t *d_run,
+                    const MTerm *mterm, const int32_t *d_deg)
+{
+    hipLaunchKernelGGL(eval_qd_arow_long_kernel, grid, block, lds, st, a, d_run, mterm, d_deg);
+}
+
+#else
+
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1)))
+eval_qd_arow_kernel(QDArgs a, const int32_t *__restrict__ d_run, const MTerm *__restrict__ mterm,
+                    const int32_t *__restrict__ d_deg)
+{
+    eval_qd_arow_body<false>(a, d_run, mterm, d_deg);
+}
+
+// Values alone: a term is one chain of products, x^a one product where the
+// power table holds it (eval_values.hip has double double).  Two waves per SIMD.
+// n = 32, 64 terms of 8 factors, 6561 points: 4.00 ms in the general kernel,
+// 2.74 ms here.
+__global__ void __launch_bounds__(512) eval_qd_values_kernel(QDArgs a, const int32_t *__restrict__ d_run,
+                                                             const MTerm *__restrict__ mterm,
+                                                             const int32_t *__restrict__ d_deg)
+{
+    extern __shared__ double xl[];
+    const char *xb = reinterpret_cast<const char *>(xl);
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int W = blockDim.x >> 6;
+    QLane ql;
+    ql.p = lane >> 1;
+    ql.c = lane & 1;
+    ql.sg = ql.c ? 0u : 0x80000000u;
+    const int64_t P = (int64_t)blockIdx.x * 32 + ql.p;
+    const bool act = P < a.npts;
+    C<4> gs;
+    qd_stage(a, xl, P, act, w, W, ql, gs);
+    const uint32_t plane = (uint32_t)a.n_var * 2048;
+
+    for (int i = blockIdx.y * W + w; i < a.n_eq; i += a.eq_stride) {
+        R<4> v = r_zero<4>();
+        const int s1 = d_run[i * DRUN + DRUN - 1];
+        for (int s = d_run[i * DRUN]; s < s1; ++s) {
+            const MTerm &r = mterm[s];
+            const int sel = r.sel, k = r.k, m = (sel >> 16) & 15;
+            if (sel & DSEL_NOVALUE) continue;
+            R<4> q = qcoef(mfast_head<0, 0, 4>(&r), ql);
+            // (a product takes longer than the loads of the next operand)
+            for (int l = 0; l < k; ++l) {
+                const bool two = (sel & (DSEL_TWO << l)) != 0;
+                const uint32_t off = l < m ? r.po[l] + (two ? 0u : plane) : r.xo[l];
+                q = pmul(q, other_signed(q, ql.sg), lds_nat(xb, off, ql.p));
+                if (two) q = pmul(q, other_signed(q, ql.sg), lds_nat(xb, r.xo[l], ql.p));
+            }
+            v = r_add<4>(v, q);
+        }
+        // total-degree start part gamma (1-t) (x_i^d - 1)
+        const int d = d_deg[i];
+        if (d > 0 && a.t) {
+            C<4> base = lds_nat(xb, (uint32_t)(i * 2048), ql.p), pw = c_from<4>(1.0, 0.0);
+            for (int e = d; e > 0; e >>= 1) {
+                if (e & 1) pw = c_mul<4>(pw, base);
+                if (e > 1) base = c_mul<4>(base, base);
+            }
+            const C<4> hv = c_mul<4>(gs, c_sub<4>(pw, c_from<4>(1.0, 0.0)));
+            v = r_add<4>(v, ql.c ? hv.im : hv.re);
+        }
+        if (act) {
+            double *hp = a.val + (int64_t)((i * 2 + ql.c) * 4) * a.ld + P;
+#pragma unroll
+            for (int l = 0; l < 4; ++l) st_nt4(hp + l * a.ld, v.v[l]);
+        }
+    }
+}
+
+int qd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t, const double *x,
+                     int64_t ld, double *val, hipStream_t st)
+{
+    QDArgs a;
+    a.t = t;
+    a.x = x;
+    a.val = val;
+    a.jac = nullptr;
+    a.npts = npts;
+    a.ld = ld;
+    a.gre = gamma ? gamma[0] : 1.0;
+    a.gim = gamma ? gamma[1] : 0.0;
+    a.n_eq = tab.n_eq;
+    a.n_var = tab.n_var;
+    a.planes = tab.dfast_planes;
+    const size_t lds = ((size_t)tab.dfast_planes * tab.n_var * 8 + 8) * 32 * sizeof(double);
+    const int64_t tiles = (npts + 31) / 32;
+    const EvalFit ft = eval_fit(tab, tiles, 8, 0, 8, lds, 20.0, 1.0);
+    const int W = ft.W, G = ft.G;
+    a.eq_stride = G * W;
+    hipLaunchKernelGGL(eval_qd_values_kernel, dim3((unsigned)tiles, (unsigned)G), dim3(64 * W), lds, st, a, tab.d_run,
+                       tab.mterm, tab.d_deg);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "eval_qd_values_kernel launch");
+    return PH_OK;
+}
+
 int qd_fast_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t,
                    const double *x, int64_t ld, double *val, double *jac, int W, int G,
                    hipStream_t st)
@@ -342,17 +467,29 @@ int qd_fast_launch(const DevTable &tab, const double gamma[2], int64_t npts, con
     a.n_eq = tab.n_eq;
     a.n_var = tab.n_var;
     a.planes = tab.dfast_planes;
-    W = W < 1 ? 1 : (W > 4 ? 4 : W);
-    if (W > tab.n_eq) W = tab.n_eq;
-    if (G < 1) G = 1;
-    while (G > 1 && G * W > tab.n_eq) G >>= 1;
-    a.eq_stride = G * W;
     const size_t lds = ((size_t)tab.dfast_planes * tab.n_var * 8 + 8) * 32 * sizeof(double);
+    // one wave per SIMD, at most four waves per workgroup; staging: about twenty
+    // products' time to read the points, and a product per power
+    if (W > 4) W = 4;
+    if (W > tab.n_eq) W = tab.n_eq;
+    if (W < 1 || G < 1) {
+        const EvalFit ft = eval_fit(tab, (npts + 31) / 32, 4, W, 4, lds, 20.0, 1.0);
+        if (W < 1) W = ft.W;
+        if (G < 1) G = ft.G;
+    } else {
+        while (G > 1 && G * W > tab.n_eq) G >>= 1;
+    }
+    a.eq_stride = G * W;
     dim3 grid((unsigned)((npts + 31) / 32), (unsigned)G);
-    hipLaunchKernelGGL(eval_qd_arow_kernel, grid, dim3(64 * W), lds, st, a, tab.d_run, tab.mterm, tab.d_deg);
+    if (tab.dlong)
+        qd_long_launch(grid, dim3(64 * W), lds, st, a, tab.d_run, tab.mterm, tab.d_deg);
+    else
+        hipLaunchKernelGGL(eval_qd_arow_kernel, grid, dim3(64 * W), lds, st, a, tab.d_run, tab.mterm, tab.d_deg);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "eval_qd_arow_kernel launch");
     return PH_OK;
 }
+
+#endif
 
 }  // namespace ph

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <map>
 #include <memory>
@@ -48,10 +49,20 @@ int hip_fail(hipError_t e, const char *what);
 constexpr int DRUN = 46;
 inline constexpr int drun_group(int k, int m) { return k * (k + 1) / 2 + m; }
 
+// A term of 9 to 16 factors of exponent 1 is two records of half the factors
+// each, the other half's factors in the place of the powers; the second adds
+// no value.  A quarter more products than one sweep, with the row on chip: n =
+// 10, terms of up to 10 factors, 34940 points, general or register-row kernel and
+// this: 154 and 34 us in double, 393 and 150 us in double double, 1.95 and 1.05
+// ms in quad double.
+constexpr int32_t DSEL_NOVALUE = 2;
+// DSEL_TWO << l: factor l < m has no x^a in the power table, its value takes
+// the products by x^(a-1) (or the other half's factor) and by x.
+constexpr int32_t DSEL_TWO = 1 << 8;
 struct DTerm {
     double cre, cim;
     int32_t k;
-    int32_t sel;     // bit 0: start term; bits 8..11: factors with a >= 3; 16..19: with a >= 2
+    int32_t sel;     // bit 0: start term; DSEL_NOVALUE; DSEL_TWO; bits 16..19: m
     uint32_t xo[8];  // LDS byte offset of the factor's coordinate x_v (v * 1024)
     uint32_t po[8];  // LDS byte offset of x_v^(a-1), or of the ones row for a = 1
     uint32_t j2[8];  // 2 * v: register index of column v in the pinned row
@@ -109,6 +120,7 @@ struct DevTable {
     int n_eq = 0, n_var = 0, kmax = 0;
     int emax = 0;                // largest exponent of a target/start term
     bool dfast = false;          // the fast-path records below are valid
+    bool dlong = false;          // records of terms with more than 8 factors among them
     int dfast_planes = 0;        // power planes staged in LDS (x, x^2, x^3)
     int32_t *d_eq_off = nullptr; // [n_eq + 1] offsets into dterm
     DTerm *dterm = nullptr;      // fast-path records (target terms, custom start terms)
@@ -125,6 +137,10 @@ struct DevTable {
     uint32_t *fac8 = nullptr;    // [n_terms][8]: each term's factor words, zero padded (tracker)
     double *coef = nullptr;      // [n_terms][2][4] limbs
     bool coef_single = false;    // every coefficient is an FP64 number
+    int cus = 256;               // compute units of the device
+    // fast path: mean over the G groups of the work of a workgroup's slowest
+    // wave with min(2^c, n_eq) waves, at [c][G - 1]
+    std::vector<float> fit[4], fit_max[4];  // (and the slowest of the groups)
     WideDev wide{};              // square systems of n <= 32, k <= 8 (rounds 0: none)
     int32_t *zc_off = nullptr;   // [n_eq + 1] columns of each row no term touches
     int32_t *zc = nullptr;
@@ -137,6 +153,66 @@ struct DevTable {
     void *u_scratch = nullptr;   // grow-only intermediate arrays of the unfused design,
     size_t u_scratch_bytes = 0;  //   sized by ph_eval_prepare (never by an evaluation)
 };
+
+// Waves per workgroup and equation groups of a fast-path launch where the
+// configuration names none.  A workgroup of W waves stages a tile of points and
+// takes every G-th run of W equations; a CU holds `waves` waves of the kernel
+// and as many workgroups as their LDS allows.  The launch takes the number of
+// rounds of workgroups times the work of one, which is that of its slowest wave
+// (DevTable::fit, in complex products) and the staging; the choice begins with
+// the largest W and one group, and another must win 3 %.  Measured against the
+// largest W and one group (double: enough groups for 1024 workgroups), n = 32
+// with 64 terms of 8 factors: 1000 points 1.53 -> 0.20 ms in double double, 7.97
+// -> 1.04 ms in quad double; 4999 points 1.55 -> 0.60 and 8.0 -> 5.2; 50000
+// points 0.751 -> 0.669 in double, 6.5 -> 5.0 in double double.
+struct EvalFit {
+    int W, G;
+};
+inline EvalFit eval_fit(const DevTable &tab, int64_t tiles, int max_w, int fixed_w, int waves, size_t lds,
+                        double stage, double even)
+{
+    EvalFit best{1, 1};
+    double best_t = -1;
+    for (int c = 3; c >= 0; --c) {
+        const int W = std::min(1 << c, tab.n_eq);
+        if ((1 << c) > max_w || (fixed_w > 0 && (1 << c) > fixed_w) || (c > 0 && W <= 1 << (c - 1))) continue;
+        const int64_t fit = std::min<int64_t>(std::max(1, waves / W), std::max<int64_t>(1, (160 * 1024) / lds));
+        const int64_t slots = tab.cus * fit;
+        const double st = stage + double(tab.dfast_planes) * tab.n_var / W;
+        for (int G = 1; G <= (int)tab.fit[c].size(); ++G) {
+            const double rounds = double((tiles * G + slots - 1) / slots);
+            const double t = rounds > 1 ? rounds * (tab.fit[c][G - 1] + st) : tab.fit_max[c][G - 1] + st;
+            if (best_t < 0 || t < 0.97 * best_t) {
+                best = EvalFit{W, G};
+                // a single round of workgroups evens nothing out
+                best_t = G == 1 && tiles <= slots ? even * t : t;
+            }
+        }
+        if (fixed_w > 0) break;
+    }
+    return best;
+}
+
+// The same for the double-double values kernel: `waves` waves per CU hide each other's
+// chains, in as small workgroups as their LDS lets a CU hold them, and the
+// work of a CU is the equations of its workgroups.
+inline EvalFit values_fit(const DevTable &tab, int64_t tiles, int waves, size_t lds, double stage)
+{
+    const int fit = std::max<int>(1, (int)((160 * 1024) / lds));
+    EvalFit best{1, 1};
+    while (best.W < waves && best.W * fit < waves) best.W *= 2;
+    if (best.W > tab.n_eq) best.W = tab.n_eq;
+    const int W = best.W;
+    double best_t = -1;
+    for (int G = 1; (G - 1) * W < tab.n_eq; ++G) {
+        const double t = double((tiles * G + tab.cus - 1) / tab.cus) * (W * ((tab.n_eq + G * W - 1) / (G * W)) + stage);
+        if (best_t < 0 || t < 0.97 * best_t) {
+            best_t = t;
+            best.G = G;
+        }
+    }
+    return best;
+}
 
 // Kernel choice and tiling of one evaluation: kernel 0 automatic, 1 general
 // (Jacobian row accumulated in the output), 2 register row (double, n <= 32),
@@ -188,6 +264,11 @@ int find_table(const ph_system *target, const ph_system *start, const DevTable *
 int prepare_unfused(const ph_system *target, DevTable &tab, int prec, int64_t npts);
 // Entries of the PH_AUTOTUNE_CACHE file for this target (called at creation).
 void load_eval_cache(ph_system *s);
+// Values alone of a system with records, in double double and quad double.
+int dd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t, const double *x,
+                     int64_t ld, double *val, hipStream_t st);
+int qd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t, const double *x,
+                     int64_t ld, double *val, hipStream_t st);
 // The unfused three-kernel evaluation (kernel choice 5).
 int unfused_launch(const DevTable &tab, const double gamma[2], int prec, int64_t npts,
                    const double *t, const double *x, int64_t ld, double *val, double *jac,

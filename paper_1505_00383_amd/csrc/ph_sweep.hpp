@@ -62,6 +62,24 @@ PH_SW Num term_sweep(int k, const uint32_t *fw, Num c, XF &&X, PF &&P)
             for (int r = 1; r < e; ++r) run = num_mul(run, xl);
         }
     }
+    if constexpr (!JAC && KEEPX) {
+        // values alone of a narrow type: the last forward product and
+        // coordinate are looked up (complex double, n = 25, 60000 points: 214
+        // us, 226 us with the running product below)
+        Num f[KMAX];
+        f[0] = run;
+#pragma unroll
+        for (int l = 1; l < KMAX; ++l)
+            if (l < k) f[l] = num_mul(f[l - 1], xv[l - 1]);
+        Num last = f[0], xlast = xv[0];
+#pragma unroll
+        for (int l = 1; l < KMAX; ++l)
+            if (l == k - 1) {
+                last = f[l];
+                xlast = xv[l];
+            }
+        return num_mul(last, xlast);
+    }
 #pragma unroll
     for (int l = 0; l < KMAX; ++l) {
         if (l < k) {

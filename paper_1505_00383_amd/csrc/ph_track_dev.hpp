@@ -303,30 +303,21 @@ __device__ __forceinline__ C<L> c_sel(bool m, const C<L> &a, const C<L> &b)
 template <int K, bool HOM, int L, class XF, class PF>
 __device__ __forceinline__ C<L> lane_sweep(int k, const uint32_t *fw, C<L> run, XF &&X, PF &&P)
 {
-    constexpr bool KEEPX = L <= 2 || K <= 2;  // quad double: few registers
-    C<L> xv[KEEPX ? K : 1], q[K];
-    auto xat = [&](int l) -> C<L> {
-        if constexpr (KEEPX)
-            return xv[l];
-        else
-            return X(fac_var(fw[l]));
-    };
-    if constexpr (KEEPX) {
+    C<L> xv[K], q[K];
 #pragma unroll
-        for (int l = 0; l < K; ++l) xv[l] = X(fac_var(fw[l]));
-    }
+    for (int l = 0; l < K; ++l) xv[l] = X(fac_var(fw[l]));
 #pragma unroll
     for (int l = 0; l < K; ++l) {
         const int e = l < k ? fac_exp(fw[l]) : 1;
-        for (int r = 1; __any(r < e); ++r) run = c_sel<L>(r < e, c_mul<L>(run, xat(l)), run);
+        for (int r = 1; __any(r < e); ++r) run = c_sel<L>(r < e, c_mul<L>(run, xv[l]), run);
     }
 #pragma unroll
     for (int l = 0; l < K; ++l) {
         q[l] = run;
-        const C<L> p = c_mul<L>(run, xat(l));
+        const C<L> p = c_mul<L>(run, xv[l]);
         run = HOM ? p : c_sel<L>(l < k, p, run);
     }
-    C<L> sfx = xat(K - 1);
+    C<L> sfx = xv[K - 1];
 #pragma unroll
     for (int l = K - 1; l >= 0; --l) {
         C<L> part = q[l];
@@ -334,8 +325,8 @@ __device__ __forceinline__ C<L> lane_sweep(int k, const uint32_t *fw, C<L> run, 
             const C<L> p = c_mul<L>(part, sfx);
             part = HOM ? p : c_sel<L>(l < k - 1, p, part);
             if (l > 0) {
-                const C<L> s = c_mul<L>(sfx, xat(l));
-                sfx = HOM ? s : c_sel<L>(l < k - 1, s, xat(l));
+                const C<L> s = c_mul<L>(sfx, xv[l]);
+                sfx = HOM ? s : c_sel<L>(l < k - 1, s, xv[l]);
             }
         }
         const int e = fac_exp(fw[l]);
@@ -347,19 +338,21 @@ __device__ __forceinline__ C<L> lane_sweep(int k, const uint32_t *fw, C<L> run, 
 }
 
 // A term of k <= KMAX factors on every active lane: the straight sweep up to
-// four factors, term_sweep beyond.
+// four factors (quad double: two), term_sweep beyond.
 template <int KMAX, int L, class XF, class PF>
 __device__ __forceinline__ C<L> wave_sweep(int k, const uint32_t *fw, const C<L> &c, XF &&X, PF &&P)
 {
-    if constexpr (KMAX > 4) {
-        if (__any(k > 4)) {
+    // (a quad-double product is issue bound by itself and 450 instructions long:
+    // beyond two factors the rolled-up form serves)
+    constexpr int KS = L <= 2 ? 4 : 2;
+    if constexpr (KMAX > KS) {
+        if (__any(k > KS)) {
             if (k == 0) return c;
             return term_sweep<KMAX, true, (L <= 2)>(k, fw, c, X, P);
         }
     }
-    // (quad double: one variant per factor count, its selects are cheap)
     constexpr bool H = L <= 2;
-    if constexpr (KMAX > 2) {
+    if constexpr (KMAX > 2 && KS > 2) {
         if (__any(k > 3))
             return H && __all(k == 4) ? lane_sweep<4, H, L>(k, fw, c, X, P) : lane_sweep<4, false, L>(k, fw, c, X, P);
         if (__any(k > 2))

@@ -116,12 +116,19 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
     // exponents <= 4 (target terms, and explicit start terms); the
     // total-degree start part is evaluated analytically per equation ----
     int emax = 0;
-    bool dfast = true;
+    bool dfast = true, dlong = false;
     auto scan = [&](const HostSystem &sy) {
         for (int t = 0; t < sy.eq_term_off[sy.n_eq]; ++t) {
             int a = sy.term_fac_off[t], b = sy.term_fac_off[t + 1];
-            if (b - a > 8) dfast = false;
-            for (int q = a; q < b; ++q) emax = std::max(emax, sy.fac_exp[q]);
+            int e = 1;
+            for (int q = a; q < b; ++q) e = std::max(e, sy.fac_exp[q]);
+            emax = std::max(emax, e);
+            if (b - a > 8) {
+                // more than 8 factors: two records of half the factors each
+                // (below), up to 16 of exponent 1
+                dlong = true;
+                if (b - a > 16 || e > 1) dfast = false;
+            }
         }
     };
     scan(f);
@@ -146,44 +153,76 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
             MTerm m;
         };
         std::vector<Rec> eqrec;
+        // one record: the factors q[0..k-1] with the exponents e in the sweep
+        // (0: the partial is dropped), the first m of which have their x^(a-1),
+        // or the factor mult[l] of the term, multiplied into the coefficient
+        auto emit_rec = [&](const HostSystem &sy, int t, int k, const int *q, const int *e, int m, const int *mult,
+                            int sel) {
+            Rec rr;
+            DTerm &r = rr.d;
+            MTerm &rm = rr.m;
+            std::memset(&r, 0, sizeof r);
+            std::memset(&rm, 0, sizeof rm);
+            r.cre = sy.coef[size_t(t) * 8];
+            r.cim = sy.coef[size_t(t) * 8 + 4];
+            for (int l = 0; l < 8; ++l) rm.c[l] = sy.coef[size_t(t) * 8 + l];
+            r.k = k;
+            for (int l = 0; l < k; ++l) {
+                const int v = sy.fac_var[q[l]];
+                // power x^(a-1), the other half's factor, or ones
+                const int pl = mult ? 0 : e[l] - 2;
+                const int pv = mult ? (l < m ? sy.fac_var[mult[l]] : -1) : (e[l] == 1 ? -1 : v);
+                r.xo[l] = uint32_t(v) * 2u * 64u * 8u;
+                r.po[l] = pv < 0 ? ones_off : uint32_t((pl * nv + pv) * 2 * 64 * 8);
+                r.j2[l] = uint32_t(2 * v);
+                r.a[l] = double(e[l]);
+                rm.xo[l] = uint32_t(v) * 4u * 64u * 8u;
+                rm.po[l] = pv < 0 ? ones_off2 : uint32_t((pl * nv + pv) * 4 * 64 * 8);
+                rm.jo[l] = uint32_t(8 * v);
+                rm.a[l] = double(e[l]);
+            }
+            r.sel = sel | (m << 16);
+            for (int l = 0; l < m; ++l)
+                if (mult || e[l] > planes) r.sel |= DSEL_TWO << l;
+            rm.k = r.k;
+            rm.sel = r.sel;
+            eqrec.push_back(rr);
+        };
         auto emit_d = [&](const HostSystem &sy, int i, int sel) {
             for (int t = sy.eq_term_off[i]; t < sy.eq_term_off[i + 1]; ++t) {
-                Rec rr;
-                DTerm &r = rr.d;
-                MTerm &m = rr.m;
-                std::memset(&r, 0, sizeof r);
-                std::memset(&m, 0, sizeof m);
-                r.cre = sy.coef[size_t(t) * 8];
-                r.cim = sy.coef[size_t(t) * 8 + 4];
-                for (int l = 0; l < 8; ++l) m.c[l] = sy.coef[size_t(t) * 8 + l];
-                int a = sy.term_fac_off[t], b = sy.term_fac_off[t + 1];
-                r.k = b - a;
-                // factors by exponent, largest first: the kernel multiplies
-                // x^(a-1) from the power table for a >= 3, x itself for
-                // a = 2 and nothing for a = 1, with wave-uniform counts
-                int ord[8];
-                for (int l = 0; l < r.k; ++l) ord[l] = a + l;
-                std::stable_sort(ord, ord + r.k,
-                                 [&](int x, int y) { return sy.fac_exp[x] > sy.fac_exp[y]; });
-                int m3 = 0, m2 = 0;
-                for (int l = 0; l < r.k; ++l) {
-                    const int q = ord[l], v = sy.fac_var[q], e = sy.fac_exp[q];
-                    const uint32_t poff = e == 1 ? ones_off : uint32_t(((e - 2) * nv + v) * 2 * 64 * 8);
-                    r.xo[l] = uint32_t(v) * 2u * 64u * 8u;
-                    r.po[l] = poff;
-                    r.j2[l] = uint32_t(2 * v);
-                    r.a[l] = double(e);
-                    m.xo[l] = uint32_t(v) * 4u * 64u * 8u;
-                    m.po[l] = e == 1 ? ones_off2 : uint32_t(((e - 2) * nv + v) * 4 * 64 * 8);
-                    m.jo[l] = uint32_t(8 * v);
-                    m.a[l] = double(e);
-                    m3 += e >= 3;
-                    m2 += e >= 2;
+                const int a = sy.term_fac_off[t], b = sy.term_fac_off[t + 1];
+                int q[16], e[16];
+                for (int l = 0; l < b - a; ++l) q[l] = a + l;
+                if (b - a <= 8) {
+                    // factors by exponent, largest first: the kernel multiplies
+                    // x^(a-1) from the power table for the first m
+                    std::stable_sort(q, q + (b - a), [&](int x, int y) { return sy.fac_exp[x] > sy.fac_exp[y]; });
+                    int m2 = 0;
+                    for (int l = 0; l < b - a; ++l) {
+                        e[l] = sy.fac_exp[q[l]];
+                        m2 += e[l] >= 2;
+                    }
+                    emit_rec(sy, t, b - a, q, e, m2, nullptr, sel);
+                    continue;
                 }
-                r.sel = sel | (m3 << 8) | (m2 << 16);
-                m.k = r.k;
-                m.sel = r.sel;
-                eqrec.push_back(rr);
+                // c A B with A and B half the factors each: the sweep of A with
+                // B's factors multiplied into the coefficient gives the value
+                // and the partials of A, the sweep of B with A's the partials
+                // of B.  An odd count has A one factor longer; the sweep of B
+                // then takes A's last factor as its first, its partial dropped.
+                const int kb = (b - a) / 2, ka = b - a - kb;
+                for (int l = 0; l < 16; ++l) e[l] = 1;
+                emit_rec(sy, t, ka, q, e, kb, q + ka, sel);
+                int qb[8], eb[8], n = 0;
+                if (ka > kb) {
+                    qb[n] = q[ka - 1];
+                    eb[n++] = 0;
+                }
+                for (int l = 0; l < kb; ++l) {
+                    qb[n] = q[ka + l];
+                    eb[n++] = 1;
+                }
+                emit_rec(sy, t, n, qb, eb, kb, q, sel | DSEL_NOVALUE);
             }
         };
         d_run.assign(size_t(ne) * DRUN, 0);
@@ -216,6 +255,32 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
         }
     }
     if (mterm.empty()) mterm.push_back(MTerm{});
+    if (dfast) {
+        // work of an equation in complex products: its records' sweeps, and a
+        // row update counted as one
+        std::vector<double> cost(ne, 0.0);
+        for (int i = 0; i < ne; ++i)
+            for (int r = d_eq_off[i]; r < d_eq_off[i + 1]; ++r)
+                cost[i] += 4.0 * dterm[r].k + ((dterm[r].sel >> 16) & 15) + 1.0;
+        for (int c = 0; c < 4; ++c) {
+            const int W = std::min(1 << c, ne);
+            for (int G = 1; (G - 1) * W < ne; ++G) {
+                double sum = 0, top = 0;
+                for (int g = 0; g < G; ++g) {
+                    double worst = 0;
+                    for (int w = 0; w < W; ++w) {
+                        double mine = 0;
+                        for (int i = g * W + w; i < ne; i += G * W) mine += cost[i];
+                        worst = std::max(worst, mine);
+                    }
+                    sum += worst;
+                    top = std::max(top, worst);
+                }
+                out.fit[c].push_back(float(sum / G));
+                out.fit_max[c].push_back(float(top));
+            }
+        }
+    }
 
     // ---- the unfused design: one slot per term value and per partial,
     // and for every output entry the list of slots summed into it ----
@@ -334,8 +399,14 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
     out.coef_single = true;
     for (size_t q = 0; q < coef.size(); ++q)
         if (q % 4 != 0 && coef[q] != 0.0) out.coef_single = false;
+    {
+        int dev = 0;
+        PH_HIP(hipGetDevice(&dev));
+        PH_HIP(hipDeviceGetAttribute(&out.cus, hipDeviceAttributeMultiprocessorCount, dev));
+    }
     out.emax = emax;
     out.dfast = dfast;
+    out.dlong = dlong;
     out.dfast_planes = planes;
     out.d_eq_off = reinterpret_cast<int32_t *>(dev + o_deo);
     out.dterm = reinterpret_cast<DTerm *>(dev + o_dt);
