@@ -69,7 +69,7 @@ __device__ __forceinline__ R<4> qd_axpy(const R<4> &r, double e, const R<4> &p)
     two_sum(s2, u3, s2, w5);
     double s3 = __builtin_fma(e, p.v[3], r.v[3]);
     s3 += E2 + ((w1 + w2) + (w3 + w4)) + w5;
-    return qd_renorm_safe(s0, s1, s2, s3, 0.0);
+    return qd_renorm_safe(s0, s1, s2, s3);
 }
 
 // the partner lane's value (the other component of the same point).  Every

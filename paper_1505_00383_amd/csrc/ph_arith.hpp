@@ -79,23 +79,23 @@ PH_HD R<L> r_neg(R<L> a)
     return a;
 }
 
-// Renormalise five level-ordered components (c0 of order 1, c_k of order
-// eps^k) into four limbs.  Pass 1 runs FastTwoSum from the bottom up, which
-// leaves c0 = the rounded total and every c_k a rounding error no larger than
-// half an ulp of the partial sum above it; pass 2 runs TwoSum over c1..c4
-// from the bottom up, which closes any gap (a tiny c1 above a larger c2) so
-// that |c_{k+1}| <= ulp(c_k).  The last component is folded in rounded.
-PH_HD R<4> qd_renorm(double c0, double c1, double c2, double c3, double c4)
+// Renormalise level-ordered components (c0 of order 1, c_k of order eps^k) into
+// four limbs.  Pass 1 runs FastTwoSum from the bottom up, which leaves c0 = the
+// rounded total and every c_k a rounding error no larger than half an ulp of
+// the partial sum above it; pass 2 runs TwoSum over c1.. from the bottom up,
+// which closes any gap (a tiny c1 above a larger c2) so that |c_{k+1}| <=
+// ulp(c_k).  (Written with a zero fifth component this took thirteen operations
+// more, of the 233 of a component of a complex product: the compiler may not
+// drop x + 0.0.  The n = 32 evaluation of 4999 points: 5.20 ms with, 4.87 ms
+// without, same bits.)
+PH_HD R<4> qd_renorm(double c0, double c1, double c2, double c3)
 {
     double s;
-    fast_two_sum(c3, c4, s, c4);
-    fast_two_sum(c2, s, s, c3);
+    fast_two_sum(c2, c3, s, c3);
     fast_two_sum(c1, s, s, c2);
     fast_two_sum(c0, s, c0, c1);
-    two_sum(c3, c4, s, c4);
-    two_sum(c2, s, s, c3);
+    two_sum(c2, c3, s, c3);
     two_sum(c1, s, c1, c2);
-    c3 += c4;
     R<4> r;
     r.v[0] = c0;
     r.v[1] = c1;
@@ -106,6 +106,23 @@ PH_HD R<4> qd_renorm(double c0, double c1, double c2, double c3, double c4)
 
 // The same when cancellation may have left a leading component smaller than a
 // trailing one (after a subtraction): TwoSum in both passes.
+PH_HD R<4> qd_renorm_safe(double c0, double c1, double c2, double c3)
+{
+    double s;
+    two_sum(c2, c3, s, c3);
+    two_sum(c1, s, s, c2);
+    two_sum(c0, s, c0, c1);
+    two_sum(c2, c3, s, c3);
+    two_sum(c1, s, c1, c2);
+    R<4> r;
+    r.v[0] = c0;
+    r.v[1] = c1;
+    r.v[2] = c2;
+    r.v[3] = c3;
+    return r;
+}
+
+// And of five components, the last folded in rounded.
 PH_HD R<4> qd_renorm_safe(double c0, double c1, double c2, double c3, double c4)
 {
     double s;
@@ -203,7 +220,7 @@ PH_HD R<L> r_mul(R<L> a, R<L> b)
         two_sum(c2, u1, c2, w4);
         two_sum(c2, u2, c2, w5);
         c3 += ((w0 + w1) + (w2 + w3)) + (w4 + w5);
-        return qd_renorm(p00, c1, c2, c3, 0.0);
+        return qd_renorm(p00, c1, c2, c3);
     }
 }
 
@@ -230,7 +247,7 @@ PH_HD R<L> r_mul_d(R<L> a, double b)
         two_sum(p2, q1, c2, w0);
         two_sum(c2, u, c2, w1);
         c3 += w0 + w1;
-        return qd_renorm(p0, c1, c2, c3, 0.0);
+        return qd_renorm(p0, c1, c2, c3);
     }
 }
 
@@ -297,7 +314,7 @@ PH_HD R<4> qd_dot2(const R<4> &a, const R<4> &b, const R<4> &c, const R<4> &d)
     s3 += ((e02 + e11) + (e20 + f02)) + ((f11 + f20) + (w[0] + w[1]));
     s3 += ((w[2] + w[3]) + (w[4] + w[5])) + ((w[6] + w[7]) + (w[8] + w[9]));
     s3 += ((w[10] + w[11]) + (w[12] + w[13])) + w[14];
-    return qd_renorm_safe(s0, s1, s2, s3, 0.0);
+    return qd_renorm_safe(s0, s1, s2, s3);
 }
 
 // ---------------------------------------------------------------------------
