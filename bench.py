@@ -46,29 +46,29 @@ PREC_NAME = {1: "complex double", 2: "complex double double", 4: "complex quad d
 TRAFFIC = {
     # the double kernel writes H and J once whatever its tiling
     "eval_d_pinned_kernel": {
-        "bytes": 41433088 + 1107386368,   # read + write
-        "sources": {"paper_1505_00383_amd/csrc/eval.hip": "a2fa63e42cb509a8",
-                    "paper_1505_00383_amd/csrc/ph_arith.hpp": "1f4274c3666f77a9",
-                    "paper_1505_00383_amd/csrc/ph_sweep.hpp": "afaab2dda7ee3e60",
-                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "ab9104fb80a39058"},
+        "bytes": 41590784 + 1107663104,   # read + write
+        "sources": {"paper_1505_00383_amd/csrc/eval.hip": "352bd3852b9d6951",
+                    "paper_1505_00383_amd/csrc/ph_arith.hpp": "a0a84046184481d5",
+                    "paper_1505_00383_amd/csrc/ph_sweep.hpp": "aedc4b2bbc19440e",
+                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "0f8e3aeaab14328a"},
     },
     # the accumulation-register kernels stage x once per (point tile,
     # equation group): their reads depend on the tiling
     "eval_dd_arow_kernel": {
-        "by_launch": {(3, 4, 1): 82423040 + 2214619008, (3, 4, 2): 147354795 + 2214631893,
-                      (3, 4, 4): 281448320 + 2214658347},
-        "sources": {"paper_1505_00383_amd/csrc/eval_dd.hip": "4f9b4854ab9300ef",
+        "by_launch": {(3, 4, 1): 80850688 + 2214614784, (3, 4, 2): 147134208 + 2214619392,
+                      (3, 4, 4): 281312000 + 2214659200},
+        "sources": {"paper_1505_00383_amd/csrc/eval_dd.hip": "6215c853085b66ca",
                     "paper_1505_00383_amd/csrc/ph_arow.hpp": "aee6853f608672f7",
-                    "paper_1505_00383_amd/csrc/ph_arith.hpp": "1f4274c3666f77a9",
-                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "ab9104fb80a39058"},
+                    "paper_1505_00383_amd/csrc/ph_arith.hpp": "a0a84046184481d5",
+                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "0f8e3aeaab14328a"},
     },
     "eval_qd_arow_kernel": {
-        "by_launch": {(3, 4, 1): 170525531 + 4429184597, (3, 4, 2): 296279509 + 4429184597,
-                      (3, 4, 4): 558127869 + 4429184597},
-        "sources": {"paper_1505_00383_amd/csrc/eval_qd.hip": "fc3b726e4958d650",
+        "by_launch": {(3, 4, 1): 166918400 + 4429185024, (3, 4, 2): 296473600 + 4429185536,
+                      (3, 4, 4): 556694016 + 4429185152},
+        "sources": {"paper_1505_00383_amd/csrc/eval_qd.hip": "af1117896b2f208c",
                     "paper_1505_00383_amd/csrc/ph_arow.hpp": "aee6853f608672f7",
-                    "paper_1505_00383_amd/csrc/ph_arith.hpp": "1f4274c3666f77a9",
-                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "ab9104fb80a39058"},
+                    "paper_1505_00383_amd/csrc/ph_arith.hpp": "a0a84046184481d5",
+                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "0f8e3aeaab14328a"},
     },
 }
 
