@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "ph_accum.hpp"
 #include "ph_arith.hpp"
 #include "ph_internal.hpp"
 #include "ph_sweep.hpp"
@@ -146,55 +147,6 @@ __device__ __forceinline__ C<L> gbcast_c(C<L> v, bool mine)
         r.im.v[l] = __builtin_bit_cast(double, gbcast_bits<NP>(bi));
     }
     return r;
-}
-
-// Running sum of L-limb values, limb by limb: the rounding error of each
-// limb's sum joins the next limb (TwoSum), the last limb is summed plainly, and
-// the limbs are renormalised once at the end.  Nothing but the last limb
-// rounds, and what a term adds to the dependency chain is one addition per
-// limb, where a normalised addition is a chain of thirteen (double double).
-template <int L>
-__device__ __forceinline__ void acc_add(R<L> &s, const R<L> &u)
-{
-    if constexpr (L == 1) {
-        s.v[0] += u.v[0];
-    } else if constexpr (L == 2) {
-        double e;
-        two_sum(s.v[0], u.v[0], s.v[0], e);
-        s.v[1] += e + u.v[1];
-    } else {
-        double e0, e1, f, g, h, k;
-        two_sum(s.v[0], u.v[0], s.v[0], e0);
-        two_sum(s.v[1], u.v[1], s.v[1], e1);
-        two_sum(s.v[1], e0, s.v[1], f);
-        two_sum(s.v[2], u.v[2], s.v[2], g);
-        two_sum(s.v[2], e1, s.v[2], h);
-        two_sum(s.v[2], f, s.v[2], k);
-        s.v[3] += (u.v[3] + g) + (h + k);
-    }
-}
-
-template <int L>
-__device__ __forceinline__ R<L> acc_value(const R<L> &s)
-{
-    if constexpr (L == 1) {
-        return s;
-    } else if constexpr (L == 2) {
-        R<2> r;
-        two_sum(s.v[0], s.v[1], r.v[0], r.v[1]);
-        return r;
-    } else {
-        // limbs may overlap and cancel against each other: three passes
-        // leave the sum in the leading limbs
-        R<4> r = s;
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            two_sum(r.v[2], r.v[3], r.v[2], r.v[3]);
-            two_sum(r.v[1], r.v[2], r.v[1], r.v[2]);
-            two_sum(r.v[0], r.v[1], r.v[0], r.v[1]);
-        }
-        return r;
-    }
 }
 
 template <int L>
@@ -807,7 +759,7 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
         const int nsh = NP / sub, eq = i % sub, sr = i / sub;
         // m-th double of row `row` of the group's matrix (hand-over slots)
         auto slot = [&](int row, int m) -> double * { return W(m / (2 * LS), row) + m % (2 * LS); };
-        C<L> v = c_zero<L>();
+        Acc<L> vre = acc_zero<L>(), vim = acc_zero<L>();  // H of the equation
         if (busy && eq < n) {
             double o1, oe;
             two_sum(1.0, -tt, o1, oe);
@@ -890,8 +842,8 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                             }
                         });
                     if (sr == 0) {
-                        acc_add<L>(v.re, tv.re);
-                        acc_add<L>(v.im, tv.im);
+                        acc_add<L>(vre, tv.re);
+                        acc_add<L>(vim, tv.im);
                     } else {
 #pragma unroll
                         for (int q = 0; q < L; ++q) {
@@ -925,8 +877,8 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                                 tv.re.v[z] = *slot(hrow, z);
                                 tv.im.v[z] = *slot(hrow, L + z);
                             }
-                            acc_add<L>(v.re, tv.re);
-                            acc_add<L>(v.im, tv.im);
+                            acc_add<L>(vre, tv.re);
+                            acc_add<L>(vim, tv.im);
                         }
                     }
                     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -935,7 +887,7 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
                 }
             }
             if (sr == 0)
-                lds_put<LS>(W(NP, i), narrow<LS, L>(C<L>{r_neg<L>(acc_value<L>(v.re)), r_neg<L>(acc_value<L>(v.im))}));
+                lds_put<LS>(W(NP, i), narrow<LS, L>(C<L>{r_neg<L>(acc_value<L>(vre)), r_neg<L>(acc_value<L>(vim))}));
         }
         if (nsh > 1 && sr > 0) {
 #pragma unroll

@@ -151,7 +151,7 @@ __device__ __forceinline__ bool run_wide(const TrackArgs &a, const TrackClass &c
                 }
                 return z;
             };
-            R<L> v = r_zero<L>();  // lane 2 e + c: component c of H_e
+            Acc<L> v = acc_zero<L>();  // lane 2 e + c: component c of H_e
             for (int ch = 0; ch < wd.chunks; ++ch) {
                 const vec4i cd = tab_read(reinterpret_cast<const vec4i *>(wd.chunk), ch);
                 auto list4 = [&](int s, vec2u (&g)[4]) {
