@@ -386,6 +386,25 @@ __device__ __forceinline__ void lagrange_weights(int m, const double *T, double 
 // normalised columns need the sum, a square root, a reciprocal and a second
 // sum.  The singularity test |w_k| <= eps |A|_F is made on the squares.
 
+// Without normalised columns the group sums are products of two matrix entries:
+// entries of 1e-130 would leave a correction no quad-double digits (its sums
+// fall below the normal range), entries of 1e130 their reciprocal norm none.
+// Dividing [J | -H] by a power of two changes no bit of the solution: the
+// exponent that brings its norm near one where it is far from it (0: leave the
+// matrix alone; also where the squared norm fro2 is zero, infinite or NaN).
+__device__ __forceinline__ int mgs_exponent(double fro2)
+{
+    const bool near_one = fro2 >= 0x1p-300 && fro2 <= 0x1p300;
+    return near_one || !(fro2 > 0.0) || fro2 == INFINITY ? 0 : -(__builtin_amdgcn_frexp_exp(fro2) / 2);
+}
+
+template <int LS>
+__device__ __forceinline__ void mgs_scale(double *entry, int e)
+{
+#pragma unroll
+    for (int l = 0; l < 2 * LS; ++l) entry[l] = __builtin_amdgcn_ldexp(entry[l], e);
+}
+
 // 1 / nu of a pivot, or false when it counts as zero: not above lim2, below
 // the normal range, or NaN.
 template <int LS>
@@ -908,7 +927,10 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
             fro += w.re.v[0] * w.re.v[0] + w.im.v[0] * w.im.v[0];
         }
         fro = gsum_d<NP>(fro);
-        const double lim2 = a.eps_sing * a.eps_sing * fro;
+        const int sc = mgs_exponent(fro);
+        if (sc != 0)
+            for (int j = 0; j <= NP; ++j) mgs_scale<LS>(W(j, i), sc);
+        const double lim2 = a.eps_sing * a.eps_sing * __builtin_amdgcn_ldexp(fro, 2 * sc);
         bool sing = false;
         C<LS> acc = c_zero<LS>();  // r_{i,rhs}, then the back-substitution value
         // the column loops address LDS only, so they stay rolled (code size)

@@ -246,7 +246,13 @@ __device__ __forceinline__ bool run_wide(const TrackArgs &a, const TrackClass &c
                 fro += w.re.v[0] * w.re.v[0] + w.im.v[0] * w.im.v[0];
             }
             fro = gsum_d<NP>(fro);
-            const double lim2 = a.eps_sing * a.eps_sing * fro;
+            const int sc = __builtin_amdgcn_readfirstlane(mgs_exponent(fro));
+            if (sc != 0) {
+                for (int j = c; j <= NP; j += CW) mgs_scale<LS>(W(j, i), sc);
+                wave_handover();
+                rhs = lds_get<LS>(W(NP, i));
+            }
+            const double lim2 = a.eps_sing * a.eps_sing * __builtin_amdgcn_ldexp(fro, 2 * sc);
             bool sing = false;
             C<LS> acc = c_zero<LS>();       // r_{i,rhs}, then the back-substitution value
             if constexpr (REG) {
