@@ -548,7 +548,9 @@ __device__ __forceinline__ void dfast_sweep(const DHead &h, const DTerm *__restr
     C<1> q = cf;
 #pragma unroll
     for (int l = 0; l < K - 1; ++l) {
-        if (l >= M) {
+        if (LONG && K >= 5 && l == 0 && (h.sel & DSEL_DROP)) {
+            // no partial
+        } else if (l >= M) {
             row.cfma((int)h.j2[l], q, sf[l + 1]);
         } else {
             const C<1> part = c_mul<1>(q, sf[l + 1]);

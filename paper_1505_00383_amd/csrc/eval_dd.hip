@@ -122,7 +122,7 @@ __device__ __forceinline__ void mfast_sweep(const MHead<2> &h, const MTerm *__re
     for (int l = 0; l < K - 1; ++l) {
         const C<2> part = c_mul<2>(q, sf[l + 1]);
         q = c_mul<2>(q, xv[l]);
-        row_axpy(row, h.jo[l], h.a[l], part);
+        if (!LONG || K < 5 || l > 0 || !(h.sel & DSEL_DROP)) row_axpy(row, h.jo[l], h.a[l], part);
     }
     if (!LONG || K < 5 || !(h.sel & DSEL_NOVALUE)) val_acc(v, c_mul<2>(q, xv[K - 1]));
     row_axpy(row, h.jo[K - 1], h.a[K - 1], q);

@@ -252,7 +252,7 @@ __device__ __forceinline__ void qfast_sweep(const MHead<4> &h, const char *__res
         const R<4> qo = other_signed(q, ql.sg);
         const R<4> part = pmul(q, qo, sfn[l + 1]);
         q = pmul(q, qo, lds_nat(xb, h.xo[l], ql.p));
-        qrow_axpy(row, h.jo[l], h.a[l], part);
+        if (!LONG || K < 5 || l > 0 || !(h.sel & DSEL_DROP)) qrow_axpy(row, h.jo[l], h.a[l], part);
     }
     if (!LONG || K < 5 || !(h.sel & DSEL_NOVALUE))
         v = r_add<4>(v, pmul(q, other_signed(q, ql.sg), lds_nat(xb, h.xo[K - 1], ql.p)));

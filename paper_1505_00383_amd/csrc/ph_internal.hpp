@@ -56,13 +56,15 @@ inline constexpr int drun_group(int k, int m) { return k * (k + 1) / 2 + m; }
 // this: 154 and 34 us in double, 393 and 150 us in double double, 1.95 and 1.05
 // ms in quad double.
 constexpr int32_t DSEL_NOVALUE = 2;
+// The record's first factor belongs to the other half: no partial of it.
+constexpr int32_t DSEL_DROP = 4;
 // DSEL_TWO << l: factor l < m has no x^a in the power table, its value takes
 // the products by x^(a-1) (or the other half's factor) and by x.
 constexpr int32_t DSEL_TWO = 1 << 8;
 struct DTerm {
     double cre, cim;
     int32_t k;
-    int32_t sel;     // bit 0: start term; DSEL_NOVALUE; DSEL_TWO; bits 16..19: m
+    int32_t sel;     // bit 0: start term; DSEL_NOVALUE, DSEL_DROP, DSEL_TWO; bits 16..19: m
     uint32_t xo[8];  // LDS byte offset of the factor's coordinate x_v (v * 1024)
     uint32_t po[8];  // LDS byte offset of x_v^(a-1), or of the ones row for a = 1
     uint32_t j2[8];  // 2 * v: register index of column v in the pinned row

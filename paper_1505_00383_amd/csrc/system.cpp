@@ -153,9 +153,9 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
             MTerm m;
         };
         std::vector<Rec> eqrec;
-        // one record: the factors q[0..k-1] with the exponents e in the sweep
-        // (0: the partial is dropped), the first m of which have their x^(a-1),
-        // or the factor mult[l] of the term, multiplied into the coefficient
+        // one record: the factors q[0..k-1] with the exponents e in the sweep,
+        // the first m of which have their x^(a-1), or the factor mult[l] of
+        // the term, multiplied into the coefficient
         auto emit_rec = [&](const HostSystem &sy, int t, int k, const int *q, const int *e, int m, const int *mult,
                             int sel) {
             Rec rr;
@@ -209,20 +209,16 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
                 // B's factors multiplied into the coefficient gives the value
                 // and the partials of A, the sweep of B with A's the partials
                 // of B.  An odd count has A one factor longer; the sweep of B
-                // then takes A's last factor as its first, its partial dropped.
+                // then takes A's last factor as its first, without a partial (the
+                // sweep of A has that one, and 0 times it is NaN where it
+                // overflows).
                 const int kb = (b - a) / 2, ka = b - a - kb;
                 for (int l = 0; l < 16; ++l) e[l] = 1;
                 emit_rec(sy, t, ka, q, e, kb, q + ka, sel);
-                int qb[8], eb[8], n = 0;
-                if (ka > kb) {
-                    qb[n] = q[ka - 1];
-                    eb[n++] = 0;
-                }
-                for (int l = 0; l < kb; ++l) {
-                    qb[n] = q[ka + l];
-                    eb[n++] = 1;
-                }
-                emit_rec(sy, t, n, qb, eb, kb, q, sel | DSEL_NOVALUE);
+                int qb[8], n = 0;
+                if (ka > kb) qb[n++] = q[ka - 1];
+                for (int l = 0; l < kb; ++l) qb[n++] = q[ka + l];
+                emit_rec(sy, t, n, qb, e, kb, q, sel | DSEL_NOVALUE | (ka > kb ? DSEL_DROP : 0));
             }
         };
         d_run.assign(size_t(ne) * DRUN, 0);
