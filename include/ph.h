@@ -174,7 +174,9 @@ int ph_eval_set_config(ph_system *target, const ph_system *start, int32_t prec, 
  * ph_eval_get_config -- the configuration ph_eval_jac would use for (target,
  * start, prec): the one pinned or tuned in this handle, else the last entry
  * for these systems in the PH_AUTOTUNE_CACHE file as read when target was
- * created (which the handle then keeps); all zero: automatic.  Host-only;
+ * created (which the handle then keeps); all zero: automatic.  A choice that
+ * ph_eval_autotune made for calls without a Jacobian is returned where there
+ * is no other.  Host-only;
  * PH_EINVAL on null pointers.
  */
 int ph_eval_get_config(const ph_system *target, const ph_system *start, int32_t prec,
@@ -184,7 +186,8 @@ int ph_eval_get_config(const ph_system *target, const ph_system *start, int32_t 
  * ph_eval_autotune -- time every applicable (kernel, waves, groups) choice of
  * ph_eval_jac on the caller's buffers (same arguments as ph_eval_jac; the
  * outputs are overwritten with a valid result) and keep the fastest for
- * (target, start, prec).  With the environment variable PH_AUTOTUNE_CACHE
+ * (target, start, prec); with jac NULL for calls without a Jacobian alone.
+ * With the environment variable PH_AUTOTUNE_CACHE
  * naming a file, the choice is appended there and found again by later
  * processes (keyed by a fingerprint of the systems).  best_ms (nullable)
  * receives the average time of the chosen configuration.  Synchronises the

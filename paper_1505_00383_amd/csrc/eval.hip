@@ -764,6 +764,11 @@ static int launch2(const EvalArgs &a, int kmax, bool xlds, bool jac, int W, int 
     return launch3<L, 32>(a, xlds, jac, W, G, lds, st);
 }
 
+static bool has_values_kernel(const DevTable &tab, int prec)
+{
+    return prec > 1 && tab.n_var <= 32 && tab.dfast && tab.mfast;
+}
+
 int eval_launch(const DevTable &tab, const double gamma[2], int prec, int64_t npts,
                 const double *t, const double *x, int64_t ld, double *val, double *jac,
                 hipStream_t st, const EvalCfg *cfg)
@@ -797,7 +802,7 @@ int eval_launch(const DevTable &tab, const double gamma[2], int prec, int64_t np
     // values alone: a kernel of the records' chains of products in double
     // double and quad double, else the general kernel (the register-row kernels
     // produce the Jacobian)
-    if (!wj && (kernel == 0 || kernel == 3) && prec > 1 && tab.n_var <= 32 && tab.dfast && tab.mfast)
+    if (!wj && (kernel == 0 || kernel == 3) && has_values_kernel(tab, prec))
         return prec == 4 ? qd_values_launch(tab, gamma, npts, t, x, ld, val, st)
                          : dd_values_launch(tab, gamma, npts, t, x, ld, val, st);
     if (!wj && kernel >= 2) kernel = 1;
@@ -904,21 +909,26 @@ static int eval_check(const ph_system *target, const ph_system *start, const dou
 
 // Look up a tuned configuration: in the handle, else among the entries of
 // the PH_AUTOTUNE_CACHE file read when the target was created (memory only:
-// an evaluation never touches the file system).
-static bool eval_cfg_lookup(const ph_system *target, const ph_system *start, int prec, EvalCfg &out)
+// an evaluation never touches the file system).  A call without a Jacobian
+// looks for a choice of its own first.
+static bool eval_cfg_lookup(const ph_system *target, const ph_system *start, int prec, bool jac, EvalCfg &out)
 {
     ph_system *tg = const_cast<ph_system *>(target);
     std::lock_guard<std::mutex> lk(tg->mu);
-    auto it = tg->eval_cfg.find({start, prec});
-    if (it != tg->eval_cfg.end()) {
-        out = it->second;
+    auto find = [&](std::map<std::pair<const ph_system *, int>, EvalCfg> &mem,
+                    const std::map<std::pair<uint64_t, int>, EvalCfg> &file) {
+        auto it = mem.find({start, prec});
+        if (it != mem.end()) {
+            out = it->second;
+            return true;
+        }
+        auto ft = file.find({start ? start->h.fingerprint : 0ull, prec});
+        if (ft == file.end()) return false;
+        out = ft->second;
+        mem[{start, prec}] = out;
         return true;
-    }
-    auto ft = tg->file_cfg.find({start ? start->h.fingerprint : 0ull, prec});
-    if (ft == tg->file_cfg.end()) return false;
-    out = ft->second;
-    tg->eval_cfg[{start, prec}] = out;
-    return true;
+    };
+    return (!jac && find(tg->values_cfg, tg->file_values)) || find(tg->eval_cfg, tg->file_cfg);
 }
 
 }  // namespace ph
@@ -935,7 +945,7 @@ extern "C" int ph_eval_jac(const ph_system *target, const ph_system *start, cons
     rc = find_table(target, start, &tab);  // built by ph_system_create / ph_eval_prepare
     if (rc) return rc;
     EvalCfg cfg;
-    const bool tuned = eval_cfg_lookup(target, start, prec, cfg);
+    const bool tuned = eval_cfg_lookup(target, start, prec, jac != nullptr, cfg);
     return eval_launch(*tab, gamma, prec, npts, t, x, ld, val, jac, (hipStream_t)stream,
                        tuned ? &cfg : nullptr);
 }
@@ -968,6 +978,9 @@ extern "C" int ph_eval_set_config(ph_system *target, const ph_system *start, int
         target->eval_cfg.erase({start, prec});
     else
         target->eval_cfg[{start, prec}] = EvalCfg{kernel, waves, groups};
+    // the setting is for calls without a Jacobian too
+    target->values_cfg.erase({start, prec});
+    target->file_values.erase({start ? start->h.fingerprint : 0ull, prec});
     return PH_OK;
 }
 
@@ -977,7 +990,8 @@ extern "C" int ph_eval_get_config(const ph_system *target, const ph_system *star
     if (!target || !kernel || !waves || !groups) return fail(PH_EINVAL, "null argument");
     // the same lookup ph_eval_jac makes: the handle, else the cache file
     EvalCfg c{0, 0, 0};
-    if (!eval_cfg_lookup(target, start, prec, c)) c = EvalCfg{0, 0, 0};
+    if (!eval_cfg_lookup(target, start, prec, true, c) && !eval_cfg_lookup(target, start, prec, false, c))
+        c = EvalCfg{0, 0, 0};
     *kernel = c.kernel;
     *waves = c.W;
     *groups = c.G;
@@ -1001,14 +1015,18 @@ extern "C" int ph_eval_autotune(ph_system *target, const ph_system *start, const
     PH_HIP(hipEventCreate(&e1));
     EvalCfg best;
     double best_t = 1e300;
-    // the automatic choice where it is a kernel that cannot be asked for
+    const bool wj = jac != nullptr;
+    // the automatic choice where it is a kernel that cannot be asked for; without
+    // a Jacobian only the kernels that such a call runs
+    const bool values = !wj && has_values_kernel(*tab, prec);
     const int kernels[5] = {3, 4, 2, 1, 0};
     for (int kk : kernels) {
-        if (kk == 0 && !tab->dlong) continue;
+        if (kk == 0 ? !(wj ? tab->dlong : values) : (!wj && kk > 1)) continue;
         for (int W : {1, 2, 4, 6, 8}) {
             for (int G = 1; G <= 8; G *= 2) {
                 if (W * G > tab->n_eq) continue;
-                EvalCfg c{kk, W, G};
+                if (kk == 0 && values && W * G > 1) continue;  // its tiling is its own
+                const EvalCfg c = kk == 0 && values ? EvalCfg{0, 0, 0} : EvalCfg{kk, W, G};
                 rc = eval_launch(*tab, gamma, prec, npts, t, x, ld, val, jac, st, &c);
                 if (rc == PH_EUNSUPPORTED) break;  // this kernel does not apply
                 if (rc) goto done;
@@ -1033,11 +1051,12 @@ extern "C" int ph_eval_autotune(ph_system *target, const ph_system *start, const
     }
     {
         std::lock_guard<std::mutex> lk(target->mu);
-        target->eval_cfg[{start, prec}] = best;
+        (wj ? target->eval_cfg : target->values_cfg)[{start, prec}] = best;
     }
     if (const char *path = std::getenv("PH_AUTOTUNE_CACHE")) {
         if (FILE *f = std::fopen(path, "a")) {
-            std::fprintf(f, "eval %llx %llx %d %d %d %d %.6f\n", (unsigned long long)target->h.fingerprint,
+            std::fprintf(f, "%s %llx %llx %d %d %d %d %.6f\n", wj ? "eval" : "values",
+                         (unsigned long long)target->h.fingerprint,
                          (unsigned long long)(start ? start->h.fingerprint : 0ull), prec, best.kernel,
                          best.W, best.G, best_t);
             std::fclose(f);

@@ -246,6 +246,10 @@ struct ph_system {
     // entries of the PH_AUTOTUNE_CACHE file for this target, read once when
     // the handle is created: (start fingerprint or 0, prec) -> config
     std::map<std::pair<uint64_t, int>, ph::EvalCfg> file_cfg;
+    // the choices autotuned for calls without a Jacobian, which other calls
+    // must not take (a values kernel says nothing about the Jacobian's)
+    std::map<std::pair<const ph_system *, int>, ph::EvalCfg> values_cfg;
+    std::map<std::pair<uint64_t, int>, ph::EvalCfg> file_values;
     int device = 0;
 };
 

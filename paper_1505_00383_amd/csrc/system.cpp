@@ -485,11 +485,15 @@ void load_eval_cache(ph_system *s)
         unsigned long long a = 0, b = 0;
         int p = 0, k = 0, w = 0, g = 0;
         double ms = 0;
-        // lines "eval <target fp> <start fp> <prec> <kernel> <W> <G> <ms>";
-        // other tags (the tracker's) have their own layout
-        if (std::sscanf(line, "%15s %llx %llx %d %d %d %d %lf", tag, &a, &b, &p, &k, &w, &g, &ms) == 8 &&
-            std::strcmp(tag, "eval") == 0 && a == s->h.fingerprint)
-            s->file_cfg[{(uint64_t)b, p}] = EvalCfg{k, w, g};  // the last entry wins
+        // lines "eval <target fp> <start fp> <prec> <kernel> <W> <G> <ms>"
+        // ("values ...": calls without a Jacobian); other tags (the tracker's)
+        // have their own layout
+        if (std::sscanf(line, "%15s %llx %llx %d %d %d %d %lf", tag, &a, &b, &p, &k, &w, &g, &ms) != 8 ||
+            a != s->h.fingerprint)
+            continue;
+        // the last entry wins
+        if (std::strcmp(tag, "eval") == 0) s->file_cfg[{(uint64_t)b, p}] = EvalCfg{k, w, g};
+        if (std::strcmp(tag, "values") == 0) s->file_values[{(uint64_t)b, p}] = EvalCfg{k, w, g};
     }
     std::fclose(f);
 }
