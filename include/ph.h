@@ -184,7 +184,8 @@ int ph_eval_get_config(const ph_system *target, const ph_system *start, int32_t 
 
 /*
  * ph_eval_autotune -- time every applicable (kernel, waves, groups) choice of
- * ph_eval_jac on the caller's buffers (same arguments as ph_eval_jac; the
+ * ph_eval_jac, and each kernel's own choice of a tiling (waves and groups 0),
+ * on the caller's buffers (same arguments as ph_eval_jac; the
  * outputs are overwritten with a valid result) and keep the fastest for
  * (target, start, prec); with jac NULL for calls without a Jacobian alone.
  * With the environment variable PH_AUTOTUNE_CACHE
