@@ -843,13 +843,14 @@ int eval_launch(const DevTable &tab, const double gamma[2], int prec, int64_t np
     }
     const size_t ldsf = ((size_t)tab.dfast_planes * tab.n_var * 2 + 2) * 64 * sizeof(double);
     const bool pin16 = kernel == 3 && tab.n_var <= 16 && tab.kmax <= 2;
-    if (kernel == 3 && !pin16 && !(cfg && cfg->W > 0 && cfg->G > 0)) {
+    if (kernel == 3 && !pin16) {
         // two waves per SIMD; staging: about sixty products' time.  (The
         // 16-column kernel is bound by what it writes and keeps the counts
         // above: 0.86 ms for 2^20 points of n = 16, 0.91 ms by this choice.)
-        const EvalFit ft = eval_fit(tab, blocks, 8, cfg && cfg->W > 0 ? W : 0, 8, ldsf, 60.0, 1.11);
-        if (!(cfg && cfg->W > 0)) W = ft.W;
-        if (!(cfg && cfg->G > 0)) G = ft.G;
+        const EvalFit ft = fast_tiling(tab, blocks, cfg && cfg->W > 0 ? W : 0, cfg && cfg->G > 0 ? G : 0, W, 8, 8,
+                                       ldsf, 60.0, 1.11);
+        W = ft.W;
+        G = ft.G;
     }
     a.eq_stride = G * W;
     dim3 grid((unsigned)blocks, (unsigned)G);

@@ -470,15 +470,9 @@ int qd_fast_launch(const DevTable &tab, const double gamma[2], int64_t npts, con
     const size_t lds = ((size_t)tab.dfast_planes * tab.n_var * 8 + 8) * 32 * sizeof(double);
     // one wave per SIMD, at most four waves per workgroup; staging: about twenty
     // products' time to read the points, and a product per power
-    if (W > 4) W = 4;
-    if (W > tab.n_eq) W = tab.n_eq;
-    if (W < 1 || G < 1) {
-        const EvalFit ft = eval_fit(tab, (npts + 31) / 32, 4, W, 4, lds, 20.0, 1.0);
-        if (W < 1) W = ft.W;
-        if (G < 1) G = ft.G;
-    } else {
-        while (G > 1 && G * W > tab.n_eq) G >>= 1;
-    }
+    const EvalFit ft = fast_tiling(tab, (npts + 31) / 32, W, G, 4, 4, 4, lds, 20.0, 1.0);
+    W = ft.W;
+    G = ft.G;
     a.eq_stride = G * W;
     dim3 grid((unsigned)((npts + 31) / 32), (unsigned)G);
     if (tab.dlong)

@@ -195,6 +195,24 @@ inline EvalFit eval_fit(const DevTable &tab, int64_t tiles, int max_w, int fixed
     return best;
 }
 
+// Waves and groups of a fast-path launch for a configuration that may name
+// either: waves alone, the groups are chosen for them; groups alone, the waves
+// are the default def_w and the groups are halved until every one has W
+// equations, as when both are named.  No workgroup is left without an equation.
+inline EvalFit fast_tiling(const DevTable &tab, int64_t tiles, int cfg_w, int cfg_g, int def_w, int max_w, int waves,
+                           size_t lds, double stage, double even)
+{
+    int W = std::min({cfg_w > 0 ? cfg_w : (cfg_g > 0 ? def_w : 0), max_w, tab.n_eq}), G = cfg_g;
+    if (cfg_g > 0) {
+        while (G > 1 && G * W > tab.n_eq) G >>= 1;
+    } else {
+        const EvalFit ft = eval_fit(tab, tiles, max_w, W, waves, lds, stage, even);
+        if (W <= 0) W = ft.W;
+        for (G = ft.G; G > 1 && (G - 1) * W >= tab.n_eq;) --G;
+    }
+    return EvalFit{W, G};
+}
+
 // The same for the double-double values kernel: `waves` waves per CU hide each other's
 // chains, in as small workgroups as their LDS lets a CU hold them, and the
 // work of a CU is the equations of its workgroups.
