@@ -158,7 +158,8 @@ int ph_eval_prepare(ph_system *target, const ph_system *start, int32_t prec,
  * kernels 2, 3 and 4 produce the Jacobian: a values-only call (jac NULL)
  * runs the general kernel with the same waves and groups, or, in double double
  * and quad double under kernels 0 and 3 where the fast path applies, a kernel
- * of its own with its own tiling;
+ * of its own, also with the same waves and groups (with its own choice of
+ * them where they were autotuned on calls with a Jacobian);
  * the automatic choice also takes the fast path for terms of 9 to 16 factors
  * of exponent 1, which kernels 3 and 4 refuse;
  * waves = waves per workgroup sharing one 64-point tile (1..8, 0 default;

@@ -802,9 +802,11 @@ int eval_launch(const DevTable &tab, const double gamma[2], int prec, int64_t np
     // values alone: a kernel of the records' chains of products in double
     // double and quad double, else the general kernel (the register-row kernels
     // produce the Jacobian)
-    if (!wj && (kernel == 0 || kernel == 3) && has_values_kernel(tab, prec))
-        return prec == 4 ? qd_values_launch(tab, gamma, npts, t, x, ld, val, st)
-                         : dd_values_launch(tab, gamma, npts, t, x, ld, val, st);
+    if (!wj && (kernel == 0 || kernel == 3) && has_values_kernel(tab, prec)) {
+        const int W = cfg && !cfg->tuned ? cfg->W : 0, G = cfg && !cfg->tuned ? cfg->G : 0;
+        return prec == 4 ? qd_values_launch(tab, gamma, npts, t, x, ld, val, W, G, st)
+                         : dd_values_launch(tab, gamma, npts, t, x, ld, val, W, G, st);
+    }
     if (!wj && kernel >= 2) kernel = 1;
     // (terms of more than 8 factors: by the automatic choice only)
     if ((kernel == 3 || kernel == 4) && (!can_fast || tab.dlong))
@@ -978,7 +980,7 @@ extern "C" int ph_eval_set_config(ph_system *target, const ph_system *start, int
     if (kernel == 0 && waves == 0 && groups == 0)
         target->eval_cfg.erase({start, prec});
     else
-        target->eval_cfg[{start, prec}] = EvalCfg{kernel, waves, groups};
+        target->eval_cfg[{start, prec}] = EvalCfg{kernel, waves, groups, false};
     // the setting is for calls without a Jacobian too
     target->values_cfg.erase({start, prec});
     target->file_values.erase({start ? start->h.fingerprint : 0ull, prec});
@@ -1032,8 +1034,7 @@ extern "C" int ph_eval_autotune(ph_system *target, const ph_system *start, const
     for (int kk : kernels) {
         if (kk == 0 ? !(wj ? tab->dlong : values) : (!wj && kk > 1)) continue;
         for (const auto &wg : tilings) {
-            const EvalCfg c{kk, wg.first, wg.second};
-            if (kk == 0 && values && c.W > 0) continue;  // its tiling is its own
+            const EvalCfg c{kk, wg.first, wg.second, wj};
             rc = eval_launch(*tab, gamma, prec, npts, t, x, ld, val, jac, st, &c);
             if (rc == PH_EUNSUPPORTED) break;  // this kernel does not apply
             if (rc) goto done;

@@ -425,7 +425,7 @@ __global__ void __launch_bounds__(512) eval_qd_values_kernel(QDArgs a, const int
 }
 
 int qd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t, const double *x,
-                     int64_t ld, double *val, hipStream_t st)
+                     int64_t ld, double *val, int W, int G, hipStream_t st)
 {
     QDArgs a;
     a.t = t;
@@ -441,8 +441,9 @@ int qd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, c
     a.planes = tab.dfast_planes;
     const size_t lds = ((size_t)tab.dfast_planes * tab.n_var * 8 + 8) * 32 * sizeof(double);
     const int64_t tiles = (npts + 31) / 32;
-    const EvalFit ft = eval_fit(tab, tiles, 8, 0, 8, lds, 20.0, 1.0);
-    const int W = ft.W, G = ft.G;
+    const EvalFit ft = fast_tiling(tab, tiles, W, G, 8, 8, 8, lds, 20.0, 1.0);
+    W = ft.W;
+    G = ft.G;
     a.eq_stride = G * W;
     hipLaunchKernelGGL(eval_qd_values_kernel, dim3((unsigned)tiles, (unsigned)G), dim3(64 * W), lds, st, a, tab.d_run,
                        tab.mterm, tab.d_deg);

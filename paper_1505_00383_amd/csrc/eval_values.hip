@@ -169,7 +169,7 @@ eval_dd_values_kernel(ValArgs a, const int32_t *__restrict__ d_run, const MTerm 
 }
 
 int dd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t, const double *x,
-                     int64_t ld, double *val, hipStream_t st)
+                     int64_t ld, double *val, int W, int G, hipStream_t st)
 {
     ValArgs a;
     a.t = t;
@@ -185,8 +185,9 @@ int dd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, c
     const size_t lds = ((size_t)tab.dfast_planes * tab.n_var + 1) * 4 * 512;
     const int64_t tiles = (npts + 63) / 64;
     // four waves per SIMD; staging: about half an equation
-    const EvalFit ft = values_fit(tab, tiles, 16, lds, 0.5);
-    const int W = ft.W, G = ft.G;
+    const EvalFit ft = named_tiling(tab.n_eq, W, G, 8, 8, [&](int w) { return values_fit(tab, tiles, w, 16, lds, 0.5); });
+    W = ft.W;
+    G = ft.G;
     a.eq_stride = G * W;
     hipLaunchKernelGGL(eval_dd_values_kernel, dim3((unsigned)tiles, (unsigned)G), dim3(64 * W), lds, st, a, tab.d_run,
                        tab.mterm, tab.d_deg);

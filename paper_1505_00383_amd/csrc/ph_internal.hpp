@@ -195,32 +195,39 @@ inline EvalFit eval_fit(const DevTable &tab, int64_t tiles, int max_w, int fixed
     return best;
 }
 
-// Waves and groups of a fast-path launch for a configuration that may name
-// either: waves alone, the groups are chosen for them; groups alone, the waves
-// are the default def_w and the groups are halved until every one has W
-// equations, as when both are named.  No workgroup is left without an equation.
-inline EvalFit fast_tiling(const DevTable &tab, int64_t tiles, int cfg_w, int cfg_g, int def_w, int max_w, int waves,
-                           size_t lds, double stage, double even)
+// Waves and groups of a launch for a configuration that may name either: waves
+// alone, the groups are chosen for them (fit(W)); groups alone, the waves are
+// the default def_w and the groups are halved until every one has W equations,
+// as when both are named.  No workgroup is left without an equation.
+template <class Fit>
+EvalFit named_tiling(int n_eq, int cfg_w, int cfg_g, int def_w, int max_w, Fit &&fit)
 {
-    int W = std::min({cfg_w > 0 ? cfg_w : (cfg_g > 0 ? def_w : 0), max_w, tab.n_eq}), G = cfg_g;
+    int W = std::min({cfg_w > 0 ? cfg_w : (cfg_g > 0 ? def_w : 0), max_w, n_eq}), G = cfg_g;
     if (cfg_g > 0) {
-        while (G > 1 && G * W > tab.n_eq) G >>= 1;
+        while (G > 1 && G * W > n_eq) G >>= 1;
     } else {
-        const EvalFit ft = eval_fit(tab, tiles, max_w, W, waves, lds, stage, even);
+        const EvalFit ft = fit(W);
         if (W <= 0) W = ft.W;
-        for (G = ft.G; G > 1 && (G - 1) * W >= tab.n_eq;) --G;
+        for (G = ft.G; G > 1 && (G - 1) * W >= n_eq;) --G;
     }
     return EvalFit{W, G};
 }
+inline EvalFit fast_tiling(const DevTable &tab, int64_t tiles, int cfg_w, int cfg_g, int def_w, int max_w, int waves,
+                           size_t lds, double stage, double even)
+{
+    return named_tiling(tab.n_eq, cfg_w, cfg_g, def_w, max_w,
+                        [&](int W) { return eval_fit(tab, tiles, max_w, W, waves, lds, stage, even); });
+}
 
 // The same for the double-double values kernel: `waves` waves per CU hide each other's
-// chains, in as small workgroups as their LDS lets a CU hold them, and the
-// work of a CU is the equations of its workgroups.
-inline EvalFit values_fit(const DevTable &tab, int64_t tiles, int waves, size_t lds, double stage)
+// chains, in as small workgroups as their LDS lets a CU hold them (or of fixed_w
+// waves), and the work of a CU is the equations of its workgroups.
+inline EvalFit values_fit(const DevTable &tab, int64_t tiles, int fixed_w, int waves, size_t lds, double stage)
 {
     const int fit = std::max<int>(1, (int)((160 * 1024) / lds));
     EvalFit best{1, 1};
     while (best.W < waves && best.W * fit < waves) best.W *= 2;
+    if (fixed_w > 0) best.W = fixed_w;
     if (best.W > tab.n_eq) best.W = tab.n_eq;
     const int W = best.W;
     double best_t = -1;
@@ -239,9 +246,11 @@ inline EvalFit values_fit(const DevTable &tab, int64_t tiles, int waves, size_t 
 // 3 fast path with the row pinned in registers (double: upper architectural
 // registers; double double and quad double: accumulation registers), 4 the double fast path
 // with a compiler-held row, 5 the unfused coeff / mon / sum kernels; W waves
-// per workgroup, G equation groups (0: default).
+// per workgroup, G equation groups (0: default).  tuned: timed on calls with a
+// Jacobian, so its tiling says nothing about the values kernels.
 struct EvalCfg {
     int kernel = 0, W = 0, G = 0;
+    bool tuned = false;
 };
 
 struct HostSystem {
@@ -289,10 +298,11 @@ int prepare_unfused(const ph_system *target, DevTable &tab, int prec, int64_t np
 // Entries of the PH_AUTOTUNE_CACHE file for this target (called at creation).
 void load_eval_cache(ph_system *s);
 // Values alone of a system with records, in double double and quad double.
+// W and G as configured, 0: chosen by the launch.
 int dd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t, const double *x,
-                     int64_t ld, double *val, hipStream_t st);
+                     int64_t ld, double *val, int W, int G, hipStream_t st);
 int qd_values_launch(const DevTable &tab, const double gamma[2], int64_t npts, const double *t, const double *x,
-                     int64_t ld, double *val, hipStream_t st);
+                     int64_t ld, double *val, int W, int G, hipStream_t st);
 // The unfused three-kernel evaluation (kernel choice 5).
 int unfused_launch(const DevTable &tab, const double gamma[2], int prec, int64_t npts,
                    const double *t, const double *x, int64_t ld, double *val, double *jac,

@@ -492,8 +492,8 @@ void load_eval_cache(ph_system *s)
             a != s->h.fingerprint)
             continue;
         // the last entry wins
-        if (std::strcmp(tag, "eval") == 0) s->file_cfg[{(uint64_t)b, p}] = EvalCfg{k, w, g};
-        if (std::strcmp(tag, "values") == 0) s->file_values[{(uint64_t)b, p}] = EvalCfg{k, w, g};
+        if (std::strcmp(tag, "eval") == 0) s->file_cfg[{(uint64_t)b, p}] = EvalCfg{k, w, g, true};
+        if (std::strcmp(tag, "values") == 0) s->file_values[{(uint64_t)b, p}] = EvalCfg{k, w, g, false};
     }
     std::fclose(f);
 }
