@@ -928,7 +928,7 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
         }
         fro = gsum_d<NP>(fro);
         const int sc = mgs_exponent(fro);
-        if (sc != 0)
+        if (__builtin_expect(sc != 0, 0))  // rare: out of the loop's way
             for (int j = 0; j <= NP; ++j) mgs_scale<LS>(W(j, i), sc);
         const double lim2 = a.eps_sing * a.eps_sing * __builtin_amdgcn_ldexp(fro, 2 * sc);
         bool sing = false;
