@@ -242,11 +242,17 @@ int ph_eval_autotune(ph_system *target, const ph_system *start, const double gam
  *                   more than the launch's kernel fits on a CU at once
  *                   (registers, LDS), so every workgroup of a launch starts
  *                   with it
- *   lanes_per_path  lanes that share one path: 4, 8, 16 or 32; 0 selects a
- *                   whole wave while the paths are few (up to about 2 k paths
- *                   of n <= 4, 16 k of n <= 8, 22 k beyond), else the natural
- *                   count (the next power of two >= n, at least 4).  With 2
- *                   or 4 times the natural count, 2 or 4 lanes share each
+ *   lanes_per_path  lanes that share one path: 4, 8, 16 or 32 (at least the
+ *                   natural count, the next power of two >= n, 4 or more); 0
+ *                   selects a whole wave while the paths are few (up to 2 k
+ *                   paths of n <= 4, 16 k of n <= 8, 22 k of n <= 16 and 50 k
+ *                   beyond, with FP64 solves and terms of few factors; as few as
+ *                   an eighth of that with long terms and solves in double double
+ *                   or quad double, whose waves take more LDS), else the natural
+ *                   count, or twice it while the paths fill less than one
+ *                   wave per SIMD at the natural count and all of them are
+ *                   resident.  With 2 or 4 times the natural count, 2 or 4
+ *                   lanes share each
  *                   equation's term sweeps; a whole wave shares the sweeps of
  *                   all equations and the columns of the solve (results
  *                   unchanged bit for bit), which shortens the iterations of
@@ -316,6 +322,8 @@ int ph_track(const ph_system *target, const ph_system *start, const double gamma
  *     is loaded on that GPU and held until the process ends; the call makes no
  *     device allocation and frees nothing;
  *   - opts->schedule must be PH_SCHED_PERSISTENT (PH_EUNSUPPORTED otherwise);
+ *   - with predictor_order >= 2 and lanes_per_path 0 it never gives a path a
+ *     whole wave (the same results, slower where the paths are few);
  *   - an explicit start system must have been prepared for this target with
  *     ph_eval_prepare (PH_EINVAL otherwise; it builds its term table);
  *   - PH_EINVAL when the predictor history of the launch (3 * 2 * prec * 8

@@ -78,12 +78,10 @@ template <int L, bool MIXED>
 int track_wide_launch_t(const TrackArgs &a, int kmax, int blocks, size_t lds, hipStream_t st, int *occ);
 int track_wide_launch(const TrackArgs &a, int prec, int kmax, int blocks, size_t lds, hipStream_t st,
                       int *occ = nullptr);
-size_t track_wide_lds_bytes(int prec, int mixed, int np_max, int kmax);
 template <int L>
 size_t slot_bytes_t();
 template <int L>
 int slot_init_launch_t(void *state, int64_t nslots, hipStream_t st);
-size_t track_lds_bytes(int prec, int mixed, int np_max);
 size_t slot_bytes(int prec);
 int slot_init_launch(int prec, void *state, int64_t nslots, hipStream_t st);
 int clear_counter_launch(unsigned int *c, hipStream_t st);

@@ -6,6 +6,7 @@
 
 #include "ph_internal.hpp"
 #include "ph_track.hpp"
+#include "track_rule.hpp"
 
 namespace ph {
 
@@ -41,20 +42,6 @@ int track_wide_launch(const TrackArgs &a, int prec, int kmax, int blocks, size_t
     case 2: return track_wide_launch_t<2, false>(a, kmax, blocks, lds, st, occ);
     default: return track_wide_launch_t<4, false>(a, kmax, blocks, lds, st, occ);
     }
-}
-
-// the arrays of run_wide (ph_track_wide.hpp), partials for kmax factors a term
-size_t track_wide_lds_bytes(int prec, int mixed, int np_max, int kmax)
-{
-    const size_t l2 = 2 * (size_t)prec, ls2 = 2 * (size_t)(mixed ? 1 : prec), np = np_max;
-    return (np * l2 + (np + 1) * np * ls2 + np * ls2 + 64 * (size_t)WIDE_ROUNDS * (l2 + kmax * ls2)) * sizeof(double);
-}
-
-size_t track_lds_bytes(int prec, int mixed, int np_max)
-{
-    const int ls = mixed ? 1 : prec;
-    const size_t w = (size_t)(64 / np_max) * (np_max + 1) * np_max * 2 * ls;
-    return (64 * 2 * (size_t)prec + w) * sizeof(double);
 }
 
 size_t slot_bytes(int prec)
@@ -202,37 +189,22 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
     int dev = 0, cus = 256;
     PH_HIP(hipGetDevice(&dev));
     PH_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    // lanes per path: as asked; else a whole wave while the paths are few (a run
-    // lasts as long as its longest path, and a wave takes a path's Newton
-    // iteration in a quarter of the time); else the natural count, where a
-    // wave's lanes do less in vain.  The line lies where the two took equal
-    // time, at this many paths per resident wave (2048 of them): n = 3 between
-    // one quarter (512 paths: 1.15 ms against 0.80 ms) and two (4096: 1.09 /
-    // 1.70); n = 8 between 3 (6561 paths: 91 / 43 ms in double double, 57 / 31
-    // in double) and 26 (52488: 132 / 185); n = 16 near 12 (24576 paths: 515 /
-    // 483 ms in quad double, 157 / 172 in double; 65536: 1028 / 1232).
-    int lanes_pp = opts->lanes_per_path;
-    bool wide = false;
-    if (lanes_pp == 0) {
-        const double waves = 8.0 * cus;
-        double lanes = 0, share = 0;
-        int nat_max = 4;
-        for (int s = 0; s < nsys; ++s) {
-            if (!targets[s]) return fail(PH_EINVAL, "null target system");
-            int nat = 4;
-            while (nat < targets[s]->h.n_var) nat *= 2;
-            nat_max = std::max(nat_max, nat);
-            const double np = (double)(path_off[s + 1] - path_off[s]);
-            lanes += np * nat;
-            share += np / (waves * (nat <= 4 ? 1 : (nat <= 8 ? 8 : 11)));
-        }
-        // the history of the no-allocation scratch is bounded for the lanes of
-        // the other kernel
-        wide = share <= 1.0 && !(noalloc && opts->predictor_order > 1);
-        // where a wave per path is ruled out: twice the natural count when
-        // the paths fill less than one wave per SIMD
-        if (!wide && lanes < 64.0 * 4 * cus && 2 * nat_max <= 32) lanes_pp = 2 * nat_max;
+    // which kernel, with how many lanes per path
+    std::vector<int> n_vars;
+    int factors = start ? std::max(1, start->h.max_k) : 1;
+    for (int s = 0; s < nsys; ++s) {
+        if (!targets[s]) return fail(PH_EINVAL, "null target system");
+        n_vars.push_back(targets[s]->h.n_var);
+        factors = std::max(factors, targets[s]->h.max_k);
     }
+    int max_blocks = 0;
+    if (const char *env = std::getenv("PH_TRACK_BLOCKS")) max_blocks = std::max(0, std::atoi(env));
+    // (the history of the no-allocation scratch is bounded for the lanes of the
+    // other kernel)
+    const LaneRule rule = track_lane_rule(nsys, n_vars.data(), path_off, factors, *opts, cus, max_blocks,
+                                          noalloc && opts->predictor_order > 1);
+    const bool wide = rule.wide;
+    const int lanes_pp = rule.lanes;
 
     // ---- systems grouped by lane-count class (4, 8, 16, 32 lanes per path)
     std::vector<SysDesc> desc;
@@ -249,7 +221,6 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
         int64_t q = 0;
         for (int s = 0; s < nsys; ++s) {
             const ph_system *t = targets[s];
-            if (!t) return fail(PH_EINVAL, "null target system");
             const int n = t->h.n_var;
             if (t->h.n_eq != n) return fail(PH_EUNSUPPORTED, "tracking needs square systems");
             if (n > 32) return fail(PH_EUNSUPPORTED, "tracking is limited to n <= 32");
@@ -382,10 +353,7 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
         if (occ > 0) per_cu = std::min(per_cu, occ);
     }
     int cap = cus * per_cu;
-    if (const char *env = std::getenv("PH_TRACK_BLOCKS")) {
-        const int e = std::atoi(env);
-        if (e > 0) cap = std::min(cap, e);
-    }
+    if (max_blocks > 0) cap = std::min(cap, max_blocks);
     // the shares are rounded down and then trimmed so that the classes
     // together never exceed the cap (one workgroup over it would start only
     // when a whole CU's worth had ended)
