@@ -389,13 +389,20 @@ __device__ __forceinline__ void lagrange_weights(int m, const double *T, double 
 // Without normalised columns the group sums are products of two matrix entries:
 // entries of 1e-130 would leave a correction no quad-double digits (its sums
 // fall below the normal range), entries of 1e130 their reciprocal norm none.
-// Dividing [J | -H] by a power of two changes no bit of the solution: the
-// exponent that brings its norm near one where it is far from it (0: leave the
-// matrix alone; also where the squared norm fro2 is zero, infinite or NaN).
+// Dividing [J | -H] by a power of two changes no bit of the solution, and where
+// the squared norm fro2 is outside 2^-300 .. 2^300 mgs_exponent is the exponent
+// that brings the norm near one (0 where fro2 is zero, infinite or NaN).
+__device__ __forceinline__ unsigned mgs_high(double fro2)
+{
+    return (unsigned)(__builtin_bit_cast(unsigned long long, fro2) >> 32);
+}
+__device__ __forceinline__ bool mgs_far(unsigned high)
+{
+    return high - (unsigned)((1023 - 300) << 20) > (unsigned)(600 << 20);
+}
 __device__ __forceinline__ int mgs_exponent(double fro2)
 {
-    const bool near_one = fro2 >= 0x1p-300 && fro2 <= 0x1p300;
-    return near_one || !(fro2 > 0.0) || fro2 == INFINITY ? 0 : -(__builtin_amdgcn_frexp_exp(fro2) / 2);
+    return !(fro2 > 0.0) || fro2 == INFINITY ? 0 : -(__builtin_amdgcn_frexp_exp(fro2) / 2);
 }
 
 template <int LS>
@@ -927,10 +934,12 @@ __device__ __forceinline__ bool run_rounds(const TrackArgs &a, const TrackClass 
             fro += w.re.v[0] * w.re.v[0] + w.im.v[0] * w.im.v[0];
         }
         fro = gsum_d<NP>(fro);
-        const int sc = mgs_exponent(fro);
-        if (__builtin_expect(sc != 0, 0))  // rare: out of the loop's way
+        double lim2 = a.eps_sing * a.eps_sing * fro;
+        if (__builtin_expect(busy && mgs_far(mgs_high(fro)), 0)) {  // rare: out of the loop's way
+            const int sc = mgs_exponent(fro);
             for (int j = 0; j <= NP; ++j) mgs_scale<LS>(W(j, i), sc);
-        const double lim2 = a.eps_sing * a.eps_sing * __builtin_amdgcn_ldexp(fro, 2 * sc);
+            lim2 = a.eps_sing * a.eps_sing * __builtin_amdgcn_ldexp(fro, 2 * sc);
+        }
         bool sing = false;
         C<LS> acc = c_zero<LS>();  // r_{i,rhs}, then the back-substitution value
         // the column loops address LDS only, so they stay rolled (code size)

@@ -246,15 +246,16 @@ __device__ __forceinline__ bool run_wide(const TrackArgs &a, const TrackClass &c
                 fro += w.re.v[0] * w.re.v[0] + w.im.v[0] * w.im.v[0];
             }
             fro = gsum_d<NP>(fro);
-            const int sc = __builtin_amdgcn_readfirstlane(mgs_exponent(fro));
+            double lim2 = a.eps_sing * a.eps_sing * fro;
             // rare: out of the loop's way (in line, n = 24 in double double 440
             // ms instead of 403)
-            if (__builtin_expect(sc != 0, 0)) {
+            if (__builtin_expect(mgs_far(__builtin_amdgcn_readfirstlane(mgs_high(fro))), 0)) {
+                const int sc = mgs_exponent(fro);
                 for (int j = c; j <= NP; j += CW) mgs_scale<LS>(W(j, i), sc);
                 wave_handover();
                 rhs = lds_get<LS>(W(NP, i));
+                lim2 = a.eps_sing * a.eps_sing * __builtin_amdgcn_ldexp(fro, 2 * sc);
             }
-            const double lim2 = a.eps_sing * a.eps_sing * __builtin_amdgcn_ldexp(fro, 2 * sc);
             bool sing = false;
             C<LS> acc = c_zero<LS>();       // r_{i,rhs}, then the back-substitution value
             if constexpr (REG) {
