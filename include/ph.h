@@ -369,8 +369,10 @@ int ph_track_batch(int32_t nsys, const ph_system *const *targets, const double *
  * about `sample` paths (each system's first ones, in proportion to its path
  * count) under each candidate (schedule; for the graph schedule a fixed
  * rounds_per_launch of 8, 32 or 128 or a launch_ms of 1, 2 or 4; blocks_per_cu;
- * lanes_per_path: the natural count, twice or four times it) and writes *opts
- * with the fastest into *tuned (every other field copied).
+ * lanes_per_path: 0, the natural count (4) where 0 chooses another for the
+ * whole batch, twice or four times it) and writes *opts with the fastest into
+ * *tuned (every other field copied).  Each candidate is timed with the kernel
+ * and lanes that the whole batch takes with it.
  * With PH_AUTOTUNE_CACHE naming a file, a previous choice for the same
  * systems, path counts, prec and mixed is read from it instead of timing, and
  * a new choice is appended.  best_seconds (nullable) receives the sample's

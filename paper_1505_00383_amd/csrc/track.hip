@@ -163,13 +163,21 @@ static int noalloc_scratch_ptr(void **out)
     return PH_OK;
 }
 
+// Bound on all workgroups of a launch (0: none).
+static int env_blocks()
+{
+    const char *env = std::getenv("PH_TRACK_BLOCKS");
+    return env ? std::max(0, std::atoi(env)) : 0;
+}
+
 // noalloc: device scratch for the no-allocation entry point (its address on
-// the current device), or NULL to allocate per call.
+// the current device), or NULL to allocate per call.  given: the kernel to take,
+// else by the number of paths.
 static int track_impl(int nsys, const ph_system *const *targets, const ph_system *start,
                       const double *gammas, const int64_t *path_off, const int64_t *path_ids,
                       const double *x_start, int64_t ld, const ph_track_opts *opts, double *x_end,
                       int8_t *status, int8_t *reason, int32_t *steps, ph_track_report *rep,
-                      hipStream_t st, unsigned char *noalloc = nullptr)
+                      hipStream_t st, unsigned char *noalloc = nullptr, const LaneRule *given = nullptr)
 {
     auto t0 = std::chrono::steady_clock::now();
     if (!opts) return fail(PH_EINVAL, "null opts");
@@ -197,12 +205,12 @@ static int track_impl(int nsys, const ph_system *const *targets, const ph_system
         n_vars.push_back(targets[s]->h.n_var);
         factors = std::max(factors, targets[s]->h.max_k);
     }
-    int max_blocks = 0;
-    if (const char *env = std::getenv("PH_TRACK_BLOCKS")) max_blocks = std::max(0, std::atoi(env));
+    const int max_blocks = env_blocks();
     // (the history of the no-allocation scratch is bounded for the lanes of the
     // other kernel)
-    const LaneRule rule = track_lane_rule(nsys, n_vars.data(), path_off, factors, *opts, cus, max_blocks,
-                                          noalloc && opts->predictor_order > 1);
+    const LaneRule rule = given ? *given
+                                : track_lane_rule(nsys, n_vars.data(), path_off, factors, *opts, cus, max_blocks,
+                                                  noalloc && opts->predictor_order > 1);
     const bool wide = rule.wide;
     const int lanes_pp = rule.lanes;
 
@@ -618,46 +626,31 @@ extern "C" int ph_track_autotune(int32_t nsys, const ph_system *const *targets, 
         off[s + 1] = off[s] + m;
     }
     const int64_t ns = off[nsys];
-    int maxn = 1;
-    for (int s = 0; s < nsys; ++s) maxn = std::max(maxn, (int)targets[s]->h.n_var);
+    int maxn = 1, factors = 1;
+    std::vector<int> n_vars;
+    for (int s = 0; s < nsys; ++s) {
+        n_vars.push_back(targets[s]->h.n_var);
+        maxn = std::max(maxn, n_vars.back());
+        factors = std::max(factors, targets[s]->h.max_k);
+    }
     DevBuf bx, bst;
     PH_HIP(hipMalloc(&bx.p, sizeof(double) * (size_t)maxn * 2 * opts->prec * ns));
     PH_HIP(hipMalloc(&bst.p, (size_t)ns));
-
-    // candidates: residency-limited workgroups per CU, both schedules, the
-    // natural lane count and two or four times it (the extra lanes share each
-    // equation's term sweeps: more waves and shorter rounds for few paths)
-    int np_max = 4;
-    while (np_max < maxn) np_max *= 2;
-    // (graph schedule: fixed round counts and time budgets per launch)
-    struct Cand { int sch, rnd, bpc, lanes; double lms; };
-    std::vector<Cand> cands;
-    for (int lanes : {0, 2 * np_max, 4 * np_max}) {
-        if (lanes > 32) continue;
-        const int lcap = (int)std::max<size_t>(
-            1, (160 * 1024) / track_lds_bytes(opts->prec, opts->mixed, lanes ? lanes : np_max));
-        for (int bpc : {2, 4, 8, 12, 16})
-            if (bpc <= lcap || bpc == 2)
-                cands.push_back({PH_SCHED_PERSISTENT, opts->rounds_per_launch, bpc, lanes, opts->launch_ms});
-        for (int rnd : {8, 32, 128}) cands.push_back({PH_SCHED_GRAPH, rnd, std::min(8, lcap), lanes, 0.0});
-        for (double lms : {1.0, 2.0, 4.0}) cands.push_back({PH_SCHED_GRAPH, 32, std::min(8, lcap), lanes, lms});
-    }
+    int dev = 0, cus = 256;
+    PH_HIP(hipGetDevice(&dev));
+    PH_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const std::vector<TuneCand> cands =
+        tune_candidates(nsys, n_vars.data(), path_off, off.data(), factors, *opts, cus, env_blocks());
     double best = 1e300;
     ph_track_opts bo = *opts;
-    for (const Cand &c : cands) {
-        ph_track_opts o = *opts;
-        o.schedule = c.sch;
-        o.rounds_per_launch = c.rnd;
-        o.blocks_per_cu = c.bpc;
-        o.lanes_per_path = c.lanes;
-        o.launch_ms = c.lms;
+    for (const TuneCand &c : cands) {
         ph_track_report r;
-        rc = track_impl(nsys, targets, nullptr, gammas, off.data(), ids.data(), nullptr, ns, &o,
-                        (double *)bx.p, (int8_t *)bst.p, nullptr, nullptr, &r, st);
+        rc = track_impl(nsys, targets, nullptr, gammas, off.data(), ids.data(), nullptr, ns, &c.o,
+                        (double *)bx.p, (int8_t *)bst.p, nullptr, nullptr, &r, st, nullptr, &c.rule);
         if (rc) return rc;
         if (r.seconds < best) {
             best = r.seconds;
-            bo = o;
+            bo = c.o;
         }
     }
     *tuned = bo;

@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <cstdint>
+#include <vector>
 
 #include "../../include/ph.h"
 #include "ph_internal.hpp"
@@ -98,6 +99,79 @@ inline LaneRule track_lane_rule(int nsys, const int *n_var, const int64_t *path_
         2 * lanes <= 64.0 * resident(track_lds_bytes(o.prec, o.mixed, 2 * nat_max)))
         r.lanes = 2 * nat_max;
     return r;
+}
+
+// Workgroups that the paths keep busy: one path per wave, or 64 / lanes of each
+// lane-count class.
+inline int64_t track_workgroups(int nsys, const int *n_var, const int64_t *path_off, const LaneRule &r)
+{
+    int64_t cls[7] = {0};  // paths by log2 of the lanes
+    int64_t need = 0;
+    for (int s = 0; s < nsys; ++s) {
+        const int lanes = std::max(natural_lanes(n_var[s]), r.lanes);
+        cls[std::min(6, __builtin_ctz(lanes))] += path_off[s + 1] - path_off[s];
+    }
+    for (int c = 2; c < 7; ++c) {
+        const int per_wave = r.wide ? 1 : 64 >> c;
+        need += (cls[c] + per_wave - 1) / per_wave;
+    }
+    return need;
+}
+
+// A launch shape to time: options, and the kernel that the whole run takes
+// with them (a sample has fewer paths, and the automatic choice would take another).
+struct TuneCand {
+    ph_track_opts o;
+    LaneRule rule;
+};
+
+// The launch shapes of a run with path counts full_off, timed on a sample with path
+// counts off: the automatic lane count, the natural one (4) where that is another,
+// twice and four times the natural count; residency-limited workgroups per CU in the
+// persistent schedule (of those that launch the same grid on the sample, the
+// largest), and round counts and time budgets per launch in the graph schedule.
+inline std::vector<TuneCand> tune_candidates(int nsys, const int *n_var, const int64_t *full_off, const int64_t *off,
+                                             int kmax, const ph_track_opts &opts, int cus, int blocks)
+{
+    int np_max = 4;
+    for (int s = 0; s < nsys; ++s) np_max = std::max(np_max, natural_lanes(n_var[s]));
+    std::vector<TuneCand> cands;
+    auto make = [&](int lanes, int sch, int rnd, int bpc, double lms) {
+        TuneCand c{opts, {}};
+        c.o.schedule = sch;
+        c.o.rounds_per_launch = rnd;
+        c.o.blocks_per_cu = bpc;
+        c.o.lanes_per_path = lanes;
+        c.o.launch_ms = lms;
+        c.rule = track_lane_rule(nsys, n_var, full_off, kmax, c.o, cus, blocks, false);
+        return c;
+    };
+    auto fit = [&](const LaneRule &r) {
+        const int np = std::max(np_max, r.lanes);
+        return r.wide ? std::min(8, track_fit(track_wide_lds_bytes(opts.prec, opts.mixed, np, kmax)))
+                      : track_fit(track_lds_bytes(opts.prec, opts.mixed, np));
+    };
+    const LaneRule first = make(0, PH_SCHED_PERSISTENT, opts.rounds_per_launch, 8, opts.launch_ms).rule;
+    for (int lanes : {0, 4, 2 * np_max, 4 * np_max}) {
+        if (lanes > 32 || (lanes == 4 && !first.wide && first.lanes == 0)) continue;
+        if (lanes > 4 && !first.wide && first.lanes == lanes) continue;  // what 0 chooses
+        std::vector<TuneCand> shapes;
+        for (int bpc : {16, 12, 8, 4, 2}) {
+            const TuneCand c = make(lanes, PH_SCHED_PERSISTENT, opts.rounds_per_launch, bpc, opts.launch_ms);
+            if (bpc > fit(c.rule) && bpc != 2) continue;
+            if (!shapes.empty()) {
+                const TuneCand &b = shapes.back();
+                const int64_t need = track_workgroups(nsys, n_var, off, c.rule);
+                if (b.rule.wide == c.rule.wide && b.rule.lanes == c.rule.lanes && need <= (int64_t)cus * bpc) continue;
+            }
+            shapes.push_back(c);
+        }
+        cands.insert(cands.end(), shapes.rbegin(), shapes.rend());
+        const int bpc = std::min(8, fit(make(lanes, PH_SCHED_GRAPH, 32, 8, 0.0).rule));
+        for (int rnd : {8, 32, 128}) cands.push_back(make(lanes, PH_SCHED_GRAPH, rnd, bpc, 0.0));
+        for (double lms : {1.0, 2.0, 4.0}) cands.push_back(make(lanes, PH_SCHED_GRAPH, 32, bpc, lms));
+    }
+    return cands;
 }
 
 }  // namespace ph

@@ -31,9 +31,32 @@ extern "C" int rule(int nsys, const int *n, const int64_t *off, int kmax, int pr
 """
 
 
+TUNE = r"""
+extern "C" int tune(int nsys, const int *n, const int64_t *full, const int64_t *off, int kmax, int prec, int mixed,
+                    int *out)
+{
+    ph_track_opts o;
+    std::memset(&o, 0, sizeof o);
+    o.prec = prec;
+    o.mixed = mixed;
+    o.rounds_per_launch = 32;
+    int q = 0;
+    for (const TuneCand &c : tune_candidates(nsys, n, full, off, kmax, o, 256, 0)) {
+        const LaneRule whole = track_lane_rule(nsys, n, full, kmax, c.o, 256, 0, false);
+        const LaneRule sample = track_lane_rule(nsys, n, off, kmax, c.o, 256, 0, false);
+        const int row[8] = {c.o.schedule, c.o.blocks_per_cu, c.o.lanes_per_path, c.rule.wide, c.rule.lanes,
+                            whole.wide == c.rule.wide && whole.lanes == c.rule.lanes, sample.wide,
+                            (int)track_workgroups(nsys, n, off, c.rule)};
+        for (int v : row) out[q++] = v;
+    }
+    return q / 8;
+}
+"""
+
+
 @pytest.fixture(scope="module")
 def lib(tmp_path_factory):
-    return host_cpp.load(tmp_path_factory, "track_rule", SOURCE)
+    return host_cpp.load(tmp_path_factory, "track_rule", SOURCE + TUNE)
 
 
 def _rule(lib, n, paths, kmax=2, prec=1, mixed=0, lanes=0, per_cu=0, blocks=0, bounded=0):
@@ -81,3 +104,28 @@ def test_lanes_asked_for_and_doubled_lanes(lib):
     # doubled lanes only where every path is resident with them
     assert _rule(lib, 8, 2048, kmax=8, prec=4, bounded=1)[:2] == (False, 16)
     assert _rule(lib, 8, 2049, kmax=8, prec=4, bounded=1)[:2] == (False, 0)
+
+
+@pytest.mark.parametrize("n,full,prec,mixed", [([8], [200000], 2, 1), ([3, 8, 16], [1000, 40000, 160000], 2, 1),
+                                               ([8], [6561], 2, 1), ([16], [65536], 4, 0), ([3], [8], 1, 0),
+                                               ([24], [300000], 1, 0)])
+def test_autotuner_times_the_kernel_of_the_whole_run(lib, n, full, prec, mixed):
+    ns = np.array(n, dtype=np.int32)
+    total = sum(full)
+    frac = min(1.0, 16384 / total)
+    whole = np.concatenate([[0], np.cumsum(full)]).astype(np.int64)
+    off = np.concatenate([[0], np.cumsum([max(1, int(np.ceil(f * frac))) for f in full])]).astype(np.int64)
+    out = (ctypes.c_int * 4096)()
+    p = lambda a: a.ctypes.data_as(ctypes.c_void_p)
+    rows = lib.tune(len(ns), p(ns), p(whole), p(off), 3, prec, mixed, out)
+    cands = np.array(out[:8 * rows]).reshape(rows, 8)
+    sched, per_cu, lanes, wide, got, same, sample_wide, need = cands.T
+    assert np.all(same == 1)                     # a candidate runs as the whole run would
+    if total > 100000:                           # ... where the sample by itself would not
+        assert np.all(wide == 0) and np.any(sample_wide[lanes == 0] == 1)
+    # the natural count is among them, as 0 or by name
+    assert np.any((wide == 0) & ((got == 0) | (got == 4)))
+    assert set(lanes) <= {0, 4, 8, 16, 32} and np.all(per_cu >= 1) and np.all(per_cu <= 16)
+    # no two persistent candidates launch the same grid on the sample
+    grids = [(a, b, min(c, 256 * d)) for a, b, c, d, e in zip(wide, got, need, per_cu, sched) if e == 0]
+    assert len(set(grids)) == len(grids)
