@@ -28,13 +28,18 @@ DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-p
           "-munsafe-fp-atomics"]
 
 
-# Sources whose compiled gfx950 assembly tests/test_pinned_registers.py
-# inspects: the build keeps it (-save-temps) with a fingerprint of what it was
+# Sources whose compiled gfx950 assembly tests/test_pinned_registers*.py
+# inspect: the build keeps it (-save-temps) with a fingerprint of what it was
 # compiled from, so the check need not compile them a second time.
 ASM_KEPT = ("eval.hip", "eval_dd.hip", "eval_qd.hip")
+# The fast-path kernel with records of long terms is a second compilation of the
+# same sources, with its objects and assembly in a folder of their own.
+LONG_UNITS = ASM_KEPT
+LONG_FLAGS = ["-DPH_LONG_UNIT"]
+LONG_DIR = "long"
 
 
-def asm_fingerprint(src: str) -> str:
+def asm_fingerprint(src: str, flags=()) -> str:
     """sha256 of the source, every header beside it and the flags."""
     import hashlib
     h = hashlib.sha256()
@@ -42,20 +47,21 @@ def asm_fingerprint(src: str) -> str:
     for f in names:
         with open(os.path.join(CSRC, f), "rb") as fh:
             h.update(f.encode() + b"\0" + fh.read())
-    h.update(" ".join(COMMON + DEVICE).encode())
+    h.update(" ".join(COMMON + DEVICE + list(flags)).encode())
     return h.hexdigest()
 
 
-def kept_asm(src: str) -> str | None:
-    """Path of the device assembly the last build kept for src, if it was
-    compiled from the current sources, else None."""
+def kept_asm(src: str, long: bool = False) -> str | None:
+    """Path of the device assembly the last build kept for src (or its long-term
+    unit), if it was compiled from the current sources, else None."""
     stem = src.rsplit(".", 1)[0]
-    path = os.path.join(BUILD, f"{stem}-hip-amdgcn-amd-amdhsa-{ARCH}.s")
-    fp = os.path.join(BUILD, src + ".asm.sha256")
+    folder = os.path.join(BUILD, LONG_DIR) if long else BUILD
+    path = os.path.join(folder, f"{stem}-hip-amdgcn-amd-amdhsa-{ARCH}.s")
+    fp = os.path.join(folder, src + ".asm.sha256")
     if not (os.path.exists(path) and os.path.exists(fp)):
         return None
     with open(fp) as fh:
-        if fh.read().strip() != asm_fingerprint(src):
+        if fh.read().strip() != asm_fingerprint(src, LONG_FLAGS if long else ()):
             return None
     return path
 
@@ -65,9 +71,6 @@ def kept_asm(src: str) -> str | None:
 # parallel.
 TRACK_UNITS = {"track_unit.hip": "track", "track_wide_unit.hip": "track_wide"}
 TRACK_VARIANTS = [(L, m) for L in (1, 2, 4) for m in (1, 0)]
-# The fast-path kernel with records of long terms is a second compilation of the
-# same source.
-LONG_UNITS = ("eval.hip", "eval_dd.hip", "eval_qd.hip")
 
 
 def sources():
@@ -84,7 +87,7 @@ def sources():
         else:
             out.append((f, f + ".o", []))
             if f in LONG_UNITS:
-                out.append((f, f + ".long.o", ["-DPH_LONG_UNIT"]))
+                out.append((f, os.path.join(LONG_DIR, f + ".o"), LONG_FLAGS))
     return out
 
 
@@ -92,20 +95,20 @@ def _compile(job) -> str:
     src, oname, extra = job
     obj = os.path.join(BUILD, oname)
     lang = ["-x", "hip"] if src.endswith(".hip") else []
-    keep = ["-save-temps=obj"] if src in ASM_KEPT and not extra else []
-    fp = asm_fingerprint(src) if keep else None
+    keep = ["-save-temps=obj"] if src in ASM_KEPT else []
+    fp = asm_fingerprint(src, extra) if keep else None
     cmd = [HIPCC] + lang + COMMON + DEVICE + extra + keep + ["-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True, cwd=BUILD)
     if r.returncode != 0:
         raise RuntimeError(f"hipcc failed on {src}:\n{r.stdout}\n{r.stderr}")
     if keep:
-        with open(os.path.join(BUILD, src + ".asm.sha256"), "w") as fh:
+        with open(os.path.join(os.path.dirname(obj), src + ".asm.sha256"), "w") as fh:
             fh.write(fp + "\n")
     return obj
 
 
 def build(jobs: int | None = None, verbose: bool = True) -> str:
-    os.makedirs(BUILD, exist_ok=True)
+    os.makedirs(os.path.join(BUILD, LONG_DIR), exist_ok=True)
     srcs = sources()
     jobs = jobs or min(len(srcs), max(1, min(8, os.cpu_count() or 1)))
     with ThreadPoolExecutor(jobs) as ex:
