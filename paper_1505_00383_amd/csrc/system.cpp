@@ -37,6 +37,18 @@ void free_table(DevTable &t)
 
 static size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 
+// The factors q[0..k-1] of a term by exponent, largest first, else in their order
+// (an insertion sort: std::stable_sort allocates on every call).
+static void by_exponent(int *q, int k, const int32_t *exp)
+{
+    for (int i = 1; i < k; ++i) {
+        const int x = q[i];
+        int j = i;
+        for (; j > 0 && exp[q[j - 1]] < exp[x]; --j) q[j] = q[j - 1];
+        q[j] = x;
+    }
+}
+
 int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
 {
     const int ne = f.n_eq, nv = f.n_var;
@@ -63,7 +75,7 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
             ord[q] = q;
             extra += exp[q] - 1;
         }
-        std::stable_sort(ord, ord + k, [&](int x, int y) { return exp[x] > exp[y]; });
+        by_exponent(ord, k, exp);
         src.push_back({sel, k, extra, int(fv.size()), c});
         for (int q = 0; q < k; ++q) {
             fv.push_back(var[ord[q]]);
@@ -196,7 +208,7 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
                 if (b - a <= 8) {
                     // factors by exponent, largest first: the kernel multiplies
                     // x^(a-1) from the power table for the first m
-                    std::stable_sort(q, q + (b - a), [&](int x, int y) { return sy.fac_exp[x] > sy.fac_exp[y]; });
+                    by_exponent(q, b - a, sy.fac_exp.data());
                     int m2 = 0;
                     for (int l = 0; l < b - a; ++l) {
                         e[l] = sy.fac_exp[q[l]];
@@ -230,17 +242,20 @@ int build_table(const HostSystem &f, const HostSystem *g, DevTable &out)
             // a >= 2) so the kernel runs one straight-line loop per group
             // (a stable sort keeps the term order within a group)
             auto grp = [](const DTerm &x) { return drun_group(x.k, (x.sel >> 16) & 15); };
-            std::stable_sort(eqrec.begin(), eqrec.end(),
-                             [&](const Rec &x, const Rec &y) { return grp(x.d) < grp(y.d); });
             const size_t first = dterm.size();
+            int32_t *run = &d_run[size_t(i) * DRUN];  // first record of each group
+            for (const Rec &rr : eqrec)
+                ++run[grp(rr.d) + 1];
+            run[0] = int32_t(first);
+            for (int gg = 1; gg < DRUN; ++gg) run[gg] += run[gg - 1];
+            int32_t next[DRUN];
+            std::copy(run, run + DRUN, next);
+            dterm.resize(first + eqrec.size());
+            mterm.resize(first + eqrec.size());
             for (const Rec &rr : eqrec) {
-                dterm.push_back(rr.d);
-                mterm.push_back(rr.m);
-            }
-            for (int gg = 0; gg < DRUN; ++gg) {
-                size_t pos = first;
-                while (pos < dterm.size() && grp(dterm[pos]) < gg) ++pos;
-                d_run[size_t(i) * DRUN + gg] = int32_t(pos);
+                const int32_t at = next[grp(rr.d)]++;
+                dterm[at] = rr.d;
+                mterm[at] = rr.m;
             }
             d_eq_off[i + 1] = int32_t(dterm.size());
             d_deg[i] = (!g && ne == nv) ? f.deg[i] : 0;
