@@ -46,29 +46,30 @@ PREC_NAME = {1: "complex double", 2: "complex double double", 4: "complex quad d
 TRAFFIC = {
     # the double kernel writes H and J once whatever its tiling
     "eval_d_pinned_kernel": {
-        "bytes": 41590784 + 1107663104,   # read + write
-        "sources": {"paper_1505_00383_amd/csrc/eval.hip": "352bd3852b9d6951",
+        "bytes": 41458688 + 1107594240,   # read + write
+        "sources": {"paper_1505_00383_amd/csrc/eval.hip": "b941600d48362e26",
                     "paper_1505_00383_amd/csrc/ph_arith.hpp": "a0a84046184481d5",
                     "paper_1505_00383_amd/csrc/ph_sweep.hpp": "aedc4b2bbc19440e",
-                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "0f8e3aeaab14328a"},
+                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "ffbd1ff644f43343"},
     },
     # the accumulation-register kernels stage x once per (point tile,
-    # equation group): their reads depend on the tiling
+    # equation group): their reads depend on the tiling ((3, 0, 0): their own
+    # choice, one group of four waves on this workload)
     "eval_dd_arow_kernel": {
-        "by_launch": {(3, 4, 1): 80850688 + 2214614784, (3, 4, 2): 147134208 + 2214619392,
-                      (3, 4, 4): 281312000 + 2214659200},
-        "sources": {"paper_1505_00383_amd/csrc/eval_dd.hip": "6215c853085b66ca",
+        "by_launch": {(3, 4, 1): 81600512 + 2214619648, (3, 4, 2): 147362176 + 2214634240,
+                      (3, 4, 4): 281419008 + 2214691968, (3, 0, 0): 81371392 + 2214657664},
+        "sources": {"paper_1505_00383_amd/csrc/eval_dd.hip": "fc54a8be42d7915b",
                     "paper_1505_00383_amd/csrc/ph_arow.hpp": "aee6853f608672f7",
                     "paper_1505_00383_amd/csrc/ph_arith.hpp": "a0a84046184481d5",
-                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "0f8e3aeaab14328a"},
+                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "ffbd1ff644f43343"},
     },
     "eval_qd_arow_kernel": {
-        "by_launch": {(3, 4, 1): 166918400 + 4429185024, (3, 4, 2): 296473600 + 4429185536,
-                      (3, 4, 4): 556694016 + 4429185152},
-        "sources": {"paper_1505_00383_amd/csrc/eval_qd.hip": "af1117896b2f208c",
+        "by_launch": {(3, 4, 1): 160073600 + 4429185024, (3, 4, 2): 291824896 + 4429185408,
+                      (3, 4, 4): 556664064 + 4429185152, (3, 0, 0): 159649792 + 4429187968},
+        "sources": {"paper_1505_00383_amd/csrc/eval_qd.hip": "0408b536c83e745d",
                     "paper_1505_00383_amd/csrc/ph_arow.hpp": "aee6853f608672f7",
                     "paper_1505_00383_amd/csrc/ph_arith.hpp": "a0a84046184481d5",
-                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "0f8e3aeaab14328a"},
+                    "paper_1505_00383_amd/csrc/ph_internal.hpp": "ffbd1ff644f43343"},
     },
 }
 
